@@ -102,6 +102,20 @@ def test_bandpass_fit(env, C, K, edge):
     say(f"  err {e}")
 
 
+@pytest.mark.parametrize("n_int,rest", [(4, 0), (5, 7), (6, 0), (60, 9), (92, 3), (93, 0), (1021, 0), (1533, 15),
+                                        (3069, 0)])
+def test_bandpass_solve_sizes(env, n_int, rest):
+    """The banded solve at the edges of its blocking: n_int (+ 1 partial interval of `rest` channels) + 3
+    coefficients in blocks of three, one to 1024 of them, partly filled, and around powers of two and whole waves.
+    16-channel knots, no edges; FP32 output: half an ulp (6e-8) plus FP64 solve errors far below, bound 1e-6."""
+    torch, pk, dev = env
+    C = 16 * n_int + rest
+    h = spectra(1, C, 17 + n_int)[0]
+    say(f"solve of {n_int + (rest > 0) + 3} coefficients")
+    got = pk.bandpass_fit(torch.from_numpy(h).to(dev), 16, 0.0).cpu().numpy()
+    rel_close(got, post.bandpass_fit(h, 16, 0.0)[0], 1e-6)
+
+
 def test_bandpass_correct_and_stats(env):
     torch, pk, dev = env
     C = 131072

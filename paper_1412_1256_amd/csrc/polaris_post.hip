@@ -28,17 +28,34 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return r;
 }
 
+// Sums over the wave of sixteen values at once: at each of four halving steps (lane distance 32, 16, 8, 4) a lane
+// gives away half of its values and adds its partner's other half, then two butterfly steps; lane l ends with the
+// sum of value l / 4 in g[0] (17 exchanges, a fixed order).
+template <int HALF = 8>
+__device__ __forceinline__ void wave_sum16(double (&g)[16], const int lane) {
+  constexpr int DIST = 4 * HALF;
+  const bool up = (lane & DIST) != 0;
+#pragma unroll
+  for (int i = 0; i < HALF; ++i) {
+    const double give = up ? g[i] : g[i + HALF], keep = up ? g[i + HALF] : g[i];
+    g[i] = keep + __shfl_xor(give, DIST, 64);
+  }
+  if constexpr (HALF > 1) {
+    wave_sum16<HALF / 2>(g, lane);
+  } else {
+    g[0] += __shfl_xor(g[0], 2, 64);
+    g[0] += __shfl_xor(g[0], 1, 64);
+  }
+}
+
 __device__ __forceinline__ bool finite(double v) { return isfinite(v); }
 
 // ------------------------------------------------------------------------------------------------
 // channel averaging: bins of `factor` channels, flagged and non-finite channels left out
 
-// factor <= kSpan: a workgroup stages the span of nb = kSpan / factor whole bins of one spectrum in LDS
-// (coalesced loads).  Bins of fewer than 64 channels are then summed by one thread each, in channel order;
-// a bin of 64 or more by a wave: lane j adds the channels j, j + 64, ... in order and the 64 lane sums are
-// added by a fixed butterfly (one thread per bin had the lanes of a wave a whole bin apart in LDS, on the
-// same banks, each waiting on a chain of factor reads: 16.4 -> 9.7 us for 30 spectra at factor 256; at
-// factor 32 the wave form was slower, 9.3 against 5.7 us).
+// factor < 64: a workgroup stages the span of nb = kSpan / factor whole bins of one spectrum in LDS (coalesced
+// loads) and one thread sums each bin in channel order (a wave per bin was slower there: at factor 32 with 30
+// spectra of 131072 channels 9.3 against 5.7 us).
 constexpr int kSpan = 2048;
 
 __global__ void __launch_bounds__(kNT) k_chan_avg_span(ChanAvgArgs a) {
@@ -59,38 +76,57 @@ __global__ void __launch_bounds__(kNT) k_chan_avg_span(ChanAvgArgs a) {
     ok[i] = use ? 1 : 0;
   }
   __syncthreads();
-  if (F < 64) {
-    for (int b = (int)threadIdx.x; b < nbl; b += kNT) {
-      double sum = 0.0;
-      int n = 0;
-      for (int i = 0; i < F; ++i) {
-        sum += (double)v[b * F + i];
-        n += ok[b * F + i];
-      }
-      const int64_t o = s * n_bins + b0 + b;
-      a.out[o] = n ? (float)(sum / n) : NAN;
-      if (a.counts) a.counts[o] = n;
-    }
-    return;
-  }
-  const int lane = (int)threadIdx.x % 64;
-  for (int b = (int)threadIdx.x / 64; b < nbl; b += kNT / 64) {  // the same rounds for a whole wave
+  for (int b = (int)threadIdx.x; b < nbl; b += kNT) {
     double sum = 0.0;
     int n = 0;
-    for (int i = lane; i < F; i += 64) {
+    for (int i = 0; i < F; ++i) {
       sum += (double)v[b * F + i];
       n += ok[b * F + i];
     }
+    const int64_t o = s * n_bins + b0 + b;
+    a.out[o] = n ? (float)(sum / n) : NAN;
+    if (a.counts) a.counts[o] = n;
+  }
+}
+
+// 64 <= factor <= kSpan: a wave per bin, straight from memory: lane j adds the channels j, j + 64, ... in order
+// (the loads of four such rounds issued together) and the 64 lane sums are added by a fixed butterfly.  Bound by
+// the read of the spectra: 30 spectra of 131072 channels at factor 256 in 8.2 us, 1.9 TB/s (11.2 us
+// staged in LDS first, with a barrier between the read and the sums).
+__global__ void __launch_bounds__(kNT) k_chan_avg_wave(ChanAvgArgs a) {
+  const int64_t s = blockIdx.y;
+  const int F = a.factor, lane = (int)threadIdx.x % 64;
+  const int64_t n_bins = a.n_chan / F;
+  const int64_t b = (int64_t)blockIdx.x * (kNT / 64) + threadIdx.x / 64;  // the same for a whole wave
+  if (b >= n_bins) return;
+  const float* row = a.in + s * a.n_chan + b * F;
+  const uint8_t* flags = a.flags ? a.flags + b * F : nullptr;
+  double sum = 0.0;
+  int n = 0;
+  for (int i0 = lane; i0 < F; i0 += 256) {
+    float x[4];
+    bool use[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      sum += __shfl_xor(sum, o, 64);
-      n += __shfl_xor(n, o, 64);
+    for (int j = 0; j < 4; ++j) {
+      const int i = i0 + 64 * j;
+      x[j] = i < F ? row[i] : NAN;
+      use[j] = !(flags && i < F && flags[i]);
     }
-    if (lane == 0) {
-      const int64_t o = s * n_bins + b0 + b;
-      a.out[o] = n ? (float)(sum / n) : NAN;
-      if (a.counts) a.counts[o] = n;
-    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (use[j] && isfinite(x[j])) {
+        sum += (double)x[j];
+        ++n;
+      }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    sum += __shfl_xor(sum, o, 64);
+    n += __shfl_xor(n, o, 64);
+  }
+  if (lane == 0) {
+    a.out[s * n_bins + b] = n ? (float)(sum / n) : NAN;
+    if (a.counts) a.counts[s * n_bins + b] = n;
   }
 }
 
@@ -130,10 +166,9 @@ __device__ __forceinline__ void bspline4(double u, double (&b)[4]) {
 
 // One wave per knot interval j: the interval's contributions to the normal equations, Gram entries G[q][p]
 // (q <= p, ten of them) of basis functions j + q, j + p and right-hand sides r[q].  Lane l adds the channels l,
-// l + 64, ... in order; the fourteen sums are then added over the lanes together: at each of four halving steps
-// a lane gives away half of its values and adds its partner's other half (17 exchanges in all, where fourteen
+// l + 64, ... in order; the fourteen sums are then added over the lanes together (17 exchanges, where fourteen
 // whole-workgroup sums took 84 and 28 barriers).  Bound by latency: 832 intervals of 128 channels
-// in 4.8-5.8 us (one workgroup per interval 11.1 us).
+// in 3.8 us (one workgroup per interval 11.1 us).
 constexpr int kGramWaves = kNT / 64;
 
 __global__ void __launch_bounds__(kNT) k_spline_gram(SplineArgs a) {
@@ -157,18 +192,7 @@ __global__ void __launch_bounds__(kNT) k_spline_gram(SplineArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) g[10 + q] += b[q] * h;
   }
-  // after the steps of lane distance 32, 16, 8 and 4, lane l holds value l / 4
-#pragma unroll
-  for (int half = 8, dist = 32; half >= 1; half /= 2, dist /= 2) {
-    const bool up = (lane & dist) != 0;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      const double give = up ? g[i] : g[i + half], keep = up ? g[i + half] : g[i];
-      g[i] = keep + __shfl_xor(give, dist, 64);
-    }
-  }
-  g[0] += __shfl_xor(g[0], 2, 64);
-  g[0] += __shfl_xor(g[0], 1, 64);
+  wave_sum16(g, lane);  // lane l holds value l / 4
   if (lane % 4 == 0 && lane / 4 < 14) a.partial[j * 14 + lane / 4] = g[0];
 }
 
@@ -339,6 +363,22 @@ __global__ void __launch_bounds__(kNT) k_bandpass_correct(const float* __restric
   out[s * n_chan + c] = (float)((double)hk[s * n_chan + c] / (g * (double)smooth[c]));
 }
 
+// The same with four channels per thread (16-byte loads and stores): rows of whole, 16-byte aligned quadruples.
+// Bound by memory: 30 spectra of 131072 channels in 8.8 us, 3.6 TB/s (10.7 us with one channel per thread).
+__global__ void __launch_bounds__(kNT) k_bandpass_correct4(const float* __restrict__ hk, int64_t n_chan,
+                                                           const float* __restrict__ smooth,
+                                                           const double* __restrict__ gain, float* __restrict__ out) {
+  const int64_t s = blockIdx.y;
+  const int64_t c = 4 * ((int64_t)blockIdx.x * kNT + threadIdx.x);
+  if (c >= n_chan) return;
+  const double g = gain ? gain[s] : 1.0;
+  const float4 h = *reinterpret_cast<const float4*>(hk + s * n_chan + c);
+  const float4 m = *reinterpret_cast<const float4*>(smooth + c);
+  *reinterpret_cast<float4*>(out + s * n_chan + c) =
+      make_float4((float)((double)h.x / (g * (double)m.x)), (float)((double)h.y / (g * (double)m.y)),
+                  (float)((double)h.z / (g * (double)m.z)), (float)((double)h.w / (g * (double)m.w)));
+}
+
 // one workgroup per spectrum: mean of the finite channels, then the root mean square deviation from it
 __global__ void __launch_bounds__(kNT) k_band_stats(const float* __restrict__ x, int64_t n_chan,
                                                     double* __restrict__ mean_sd) {
@@ -370,7 +410,7 @@ __global__ void __launch_bounds__(kNT) k_band_stats(const float* __restrict__ x,
 // Eq. 3 / Eq. 4, block form: workgroup (chunk c, series s) covers the points t of chunk c and writes, per lag
 // L, the sum of squared second differences (x[t+L] - 2 x[t] + x[t-L])^2 over its t with all three samples
 // finite and their count, and (normalised) the sum and count of its finite points; a second kernel adds
-// the chunks of each series in order.
+// the chunks of each series.  This form takes any stride and lag.
 __global__ void __launch_bounds__(kNT) k_allan_part(AllanArgs a, int64_t chunks) {
   __shared__ double sh[kNT / 64];
   const int64_t s_ = blockIdx.x, c = blockIdx.y;
@@ -410,6 +450,108 @@ __global__ void __launch_bounds__(kNT) k_allan_part(AllanArgs a, int64_t chunks)
     if (threadIdx.x == 0) {
       out[2 * l] = s;
       out[2 * l + 1] = n;
+    }
+  }
+}
+
+// The same partial sums for series of consecutive points (point_stride 1) whose lags are at most kWinMaxLag: the
+// workgroup stages its chunk with the largest lag's points on either side in LDS (points outside the series as
+// NaN) and one sweep serves eight lags.  A chunk whose staged points are all finite takes every term untested
+// (its counts are known); any other tests each second difference.  Bound by FP64 issue, about ten operations a
+// term: 30 spectra of 131072 channels at 8 lags in
+// 19.3 us (37.6 us reading each term's three points from memory, lag by lag, with a workgroup sum per lag).
+constexpr int kChunkLags = 8;
+
+__global__ void __launch_bounds__(kNT) k_allan_chunk(AllanArgs a, int64_t chunks, int lmax) {
+  __shared__ float w[kAllanChunk + 2 * kWinMaxLag];
+  __shared__ double red[kNT / 64][2 * kChunkLags];
+  __shared__ double sh[kNT / 64];
+  const int tid = (int)threadIdx.x, lane = tid % 64;
+  const int64_t s_ = blockIdx.x, c = blockIdx.y;
+  const float* x = a.x + s_ * a.series_stride;
+  const int64_t t0 = c * kAllanChunk;
+  const int n = (int)((a.n_points - t0) < kAllanChunk ? (a.n_points - t0) : kAllanChunk);  // points of the chunk
+  bool bad = false;
+  constexpr int LD = 10;  // loads in flight per thread (two rounds at the longest lags)
+  for (int i0 = tid; i0 < n + 2 * lmax; i0 += LD * kNT) {
+    float v[LD];
+#pragma unroll
+    for (int j = 0; j < LD; ++j) {  // every load is issued, from the nearest point of the series
+      const int64_t t = t0 - lmax + i0 + j * kNT;
+      v[j] = x[t < 0 ? 0 : (t < a.n_points ? t : a.n_points - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < LD; ++j) {
+      const int i = i0 + j * kNT;
+      const int64_t t = t0 - lmax + i;
+      if (i < n + 2 * lmax) {
+        const float u = t >= 0 && t < a.n_points ? v[j] : NAN;
+        bad = bad || !isfinite(u);
+        w[i] = u;
+      }
+    }
+  }
+  const bool tested = __syncthreads_or(bad);
+  double* out = a.part + (s_ * chunks + c) * (a.n_lags + 1) * 2;
+  if (a.normalize) {
+    double s = 0.0, m = 0.0;
+    for (int t = tid; t < n; t += kNT) {
+      const float v = w[lmax + t];
+      if (isfinite(v)) {
+        s += (double)v;
+        m += 1.0;
+      }
+    }
+    s = block_sum(s, sh);
+    m = block_sum(m, sh);
+    if (tid == 0) {
+      out[2 * a.n_lags] = s;
+      out[2 * a.n_lags + 1] = m;
+    }
+  }
+  for (int l0 = 0; l0 < a.n_lags; l0 += kChunkLags) {
+    int L[kChunkLags];
+    double v[2 * kChunkLags];  // sums, then counts
+#pragma unroll
+    for (int l = 0; l < kChunkLags; ++l) {
+      L[l] = l0 + l < a.n_lags ? a.lags[l0 + l] : 0;  // 0: not a lag of this group (a zero difference)
+      v[l] = v[kChunkLags + l] = 0.0;
+    }
+    if (!tested) {
+      for (int t = tid; t < n; t += kNT) {
+        const double xt = (double)w[lmax + t];
+#pragma unroll
+        for (int l = 0; l < kChunkLags; ++l) {
+          const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
+          v[l] += d * d;
+        }
+      }
+    } else {
+      for (int t = tid; t < n; t += kNT) {
+        const double xt = (double)w[lmax + t];
+#pragma unroll
+        for (int l = 0; l < kChunkLags; ++l) {
+          const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
+          const bool use = finite(d);
+          v[l] += use ? d * d : 0.0;
+          v[kChunkLags + l] += use ? 1.0 : 0.0;
+        }
+      }
+    }
+    // sixteen sums over the wave by halving (lane l then holds value l / 4), then over the waves in order
+    wave_sum16(v, lane);
+    __syncthreads();  // the previous group's readers are done
+    if (lane % 4 == 0) red[tid / 64][lane / 4] = v[0];
+    __syncthreads();
+    if (tid < kChunkLags && l0 + tid < a.n_lags) {
+      double s = 0.0, m = 0.0;
+#pragma unroll
+      for (int k = 0; k < kNT / 64; ++k) {
+        s += red[k][tid];
+        m += red[k][kChunkLags + tid];
+      }
+      out[2 * (l0 + tid)] = s;
+      out[2 * (l0 + tid) + 1] = tested ? m : (double)n;
     }
   }
 }
@@ -454,6 +596,44 @@ __global__ void __launch_bounds__(kNT) k_allan_total(AllanArgs a, int64_t chunks
     chunk_sum(l, s, n);
     const double tau = (double)a.lags[l] * a.spacing;
     a.out[s_ * a.n_lags + l] = n > 0.0 ? s / n / (2.0 * tau * tau) / mean2 : NAN;
+  }
+}
+
+// Series of kTotalChunks or more chunks: one workgroup per series, a wave per lag in turn.  Lane l adds the
+// chunks l, l + 64, ... in order and the lanes' sums are added by a fixed butterfly (one thread per series walked
+// the chunks of its lags one batch of loads after another: 12.7 us for 30 series of 32 chunks and 8 lags, 3.8
+// here; with few chunks most lanes of a wave would have none).
+constexpr int64_t kTotalChunks = 8;
+
+__global__ void __launch_bounds__(kNT) k_allan_total_wave(AllanArgs a, int64_t chunks) {
+  const int64_t s_ = blockIdx.x;
+  const int lane = (int)threadIdx.x % 64;
+  const int64_t rec = (int64_t)(a.n_lags + 1) * 2;
+  const double* part = a.part + s_ * chunks * rec;
+  auto chunk_sum = [&](int f, double& s, double& n) {
+    s = n = 0.0;
+    for (int64_t c = lane; c < chunks; c += 64) {
+      s += part[c * rec + 2 * f];
+      n += part[c * rec + 2 * f + 1];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      s += __shfl_xor(s, o, 64);
+      n += __shfl_xor(n, o, 64);
+    }
+  };
+  double mean2 = 1.0;
+  if (a.normalize) {
+    double s, n;
+    chunk_sum(a.n_lags, s, n);
+    const double m = s / n;
+    mean2 = m * m;
+  }
+  for (int l = (int)threadIdx.x / 64; l < a.n_lags; l += kNT / 64) {
+    double s, n;
+    chunk_sum(l, s, n);
+    const double tau = (double)a.lags[l] * a.spacing;
+    if (lane == 0) a.out[s_ * a.n_lags + l] = n > 0.0 ? s / n / (2.0 * tau * tau) / mean2 : NAN;
   }
 }
 
@@ -750,7 +930,10 @@ __global__ void __launch_bounds__(kWinThreads) k_allan_window(AllanArgs a) {
 
 hipError_t launch_channel_average(const ChanAvgArgs& a, hipStream_t s) {
   const int64_t n_bins = a.n_chan / a.factor;
-  if (a.factor <= kSpan) {
+  if (a.factor >= 64 && a.factor <= kSpan) {
+    const dim3 grid((unsigned)((n_bins + kNT / 64 - 1) / (kNT / 64)), (unsigned)a.n_spec);
+    hipLaunchKernelGGL(k_chan_avg_wave, grid, dim3(kNT), 0, s, a);
+  } else if (a.factor < 64) {
     const int nb = kSpan / a.factor;
     const dim3 grid((unsigned)((n_bins + nb - 1) / nb), (unsigned)a.n_spec);
     hipLaunchKernelGGL(k_chan_avg_span, grid, dim3(kNT), 0, s, a);
@@ -800,6 +983,12 @@ hipError_t launch_bandpass_fit(const SplineArgs& a, hipStream_t s) {
 
 hipError_t launch_bandpass_correct(const float* hk, int64_t n_spec, int64_t n_chan, const float* smooth,
                                    const double* gain, float* out, hipStream_t s) {
+  const uintptr_t at = reinterpret_cast<uintptr_t>(hk) | reinterpret_cast<uintptr_t>(smooth) | reinterpret_cast<uintptr_t>(out);
+  if (n_chan % 4 == 0 && at % 16 == 0) {
+    hipLaunchKernelGGL(k_bandpass_correct4, dim3((unsigned)((n_chan / 4 + kNT - 1) / kNT), (unsigned)n_spec), dim3(kNT),
+                       0, s, hk, n_chan, smooth, gain, out);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_bandpass_correct, dim3((unsigned)((n_chan + kNT - 1) / kNT), (unsigned)n_spec), dim3(kNT), 0,
                      s, hk, n_chan, smooth, gain, out);
   return hipGetLastError();
@@ -834,8 +1023,15 @@ hipError_t launch_allan(const AllanArgs& a, hipStream_t s) {
                        dim3(kColsSeries * kColsSlices), 0, s, a);
   } else {
     const int64_t chunks = a.n_points > 0 ? (a.n_points + kAllanChunk - 1) / kAllanChunk : 1;
-    hipLaunchKernelGGL(k_allan_part, dim3((unsigned)a.n_series, (unsigned)chunks), dim3(kNT), 0, s, a, chunks);
-    hipLaunchKernelGGL(k_allan_total, dim3((unsigned)((a.n_series + kNT - 1) / kNT)), dim3(kNT), 0, s, a, chunks);
+    const dim3 grid((unsigned)a.n_series, (unsigned)chunks);
+    if (a.point_stride == 1 && lmax <= kWinMaxLag && a.n_points >= 1)
+      hipLaunchKernelGGL(k_allan_chunk, grid, dim3(kNT), 0, s, a, chunks, lmax);
+    else
+      hipLaunchKernelGGL(k_allan_part, grid, dim3(kNT), 0, s, a, chunks);
+    if (chunks >= kTotalChunks)
+      hipLaunchKernelGGL(k_allan_total_wave, dim3((unsigned)a.n_series), dim3(kNT), 0, s, a, chunks);
+    else
+      hipLaunchKernelGGL(k_allan_total, dim3((unsigned)((a.n_series + kNT - 1) / kNT)), dim3(kNT), 0, s, a, chunks);
   }
   return hipGetLastError();
 }

@@ -246,3 +246,53 @@ def test_post_reductions_are_deterministic(env):
     torch.cuda.synchronize(dev)
     for u, v in zip(a, b):
         assert torch.equal(torch.nan_to_num(u), torch.nan_to_num(v))
+
+
+@pytest.mark.parametrize("n,bad", [(1, 0), (64, 0), (1024, 3), (1026, 0), (4096, 0), (4097, 1), (4608, 0), (12289, 2),
+                                   (28672, 0), (28673, 4), (40000, 700)])
+def test_allan_consecutive_points(env, n, bad):
+    """Series of consecutive points around the edges of the 4096-point chunks and the longest staged lag (512), and
+    past it (513), with non-finite samples; the chunk sums by a thread (under 8 chunks) and by a wave per lag.
+    FP64 sums in another order: relative differences of order n eps, bound 1e-10."""
+    torch, pk, dev = env
+    rng = np.random.default_rng(n)
+    x = (1 + 0.01 * rng.standard_normal((3, n))).astype(np.float32)
+    if bad:
+        x[1, rng.integers(0, n, bad)] = np.nan
+        x[2, -bad:] = np.inf
+    for lags in ([1, 2, 3, 31, 64, 255, 511, 512, 5], [513, 7]):
+        say(f"allan n={n} bad={bad} lags={lags}")
+        for norm in (False, True):
+            with warnings.catch_warnings():
+                warnings.simplefilter("ignore")
+                ref = post.allan(x, lags, 2.0, norm)
+            got = pk.allan(torch.from_numpy(x).to(dev), lags, 2.0, normalize=norm, axis=1).cpu().numpy()
+            rel_close(got, ref, 1e-10)
+
+
+@pytest.mark.parametrize("factor,bins", [(63, 5), (64, 7), (65, 1), (255, 9), (256, 4), (257, 3), (2047, 2), (2048, 3),
+                                         (2049, 2)])
+def test_channel_average_factor_edges(env, factor, bins):
+    """Bins around the changes of form (64 and 2048 channels) and of the wave's rounds of 256, and a count of bins
+    that does not fill a workgroup; counts exact, means within one FP32 rounding (1e-6)."""
+    torch, pk, dev = env
+    x = spectra(3, factor * bins, factor, nan_edges=5)
+    flags = (np.arange(factor * bins) % 11 == 3).astype(np.uint8)
+    for fl in (None, flags):
+        out, cnt = pk.channel_average(torch.from_numpy(x).to(dev), factor,
+                                      None if fl is None else torch.from_numpy(fl).to(dev))
+        ref, rcnt = post.channel_average(x, factor, fl)
+        assert np.array_equal(cnt.cpu().numpy(), rcnt)
+        rel_close(out.cpu().numpy(), ref, 1e-6)
+
+
+@pytest.mark.parametrize("n,shift", [(4, 0), (1020, 0), (1024, 1), (1028, 0), (1030, 0), (5000, 2)])
+def test_bandpass_correct_alignment(env, n, shift):
+    """Rows of whole aligned quadruples, and rows that are not (odd lengths, buffers that start off 16 bytes)."""
+    torch, pk, dev = env
+    hk, sm = spectra(3, n, n), spectra(1, n, n + 1)[0]
+    G = np.array([1.0, 0.5, 3.0])
+    t = torch.zeros(3 * n + 4, device=dev)[shift:shift + 3 * n].view(3, n)
+    t.copy_(torch.from_numpy(hk))
+    got = pk.bandpass_correct(t, torch.from_numpy(sm).to(dev), torch.from_numpy(G).to(dev))
+    rel_close(got.cpu().numpy(), post.bandpass_correct(hk, sm, G), 1e-6)

@@ -8,6 +8,9 @@ namespace ps {
 
 constexpr int kMaxAllanLags = 64;
 constexpr int64_t kAllanChunk = 4096;  // points per workgroup of a series (block form)
+// whole-series form (side-by-side series): threads of a workgroup, and its LDS for the series (half a CU's, less
+// the partial sums)
+constexpr int kSeriesThreads = 512, kSeriesLdsBytes = 73216;
 constexpr int kWinMaxLag = 512;        // largest lag of the LDS-window form (side-by-side series)
 constexpr int64_t kMaxSplineCoef = 3072;  // basis functions of one bandpass fit (LDS of the solve)
 
@@ -36,6 +39,7 @@ struct AllanArgs {
   int32_t n_lags;
   int32_t normalize;
   int32_t lags[kMaxAllanLags];
+  int32_t runs[kMaxAllanLags];  // whole-series form: runs per residue of each lag (set by the launcher)
   double spacing;
   double* out;              // [n_series][n_lags]
   double* part;             // [n_series][chunks][n_lags + 1][2]: per chunk sums and counts (block form)

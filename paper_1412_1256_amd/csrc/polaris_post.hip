@@ -4,6 +4,8 @@
 // latency-bound; sums are FP64 in a fixed order (run-to-run identical results).
 #include "polaris_post.h"
 
+#include "polaris_device.h"
+
 #include <math.h>
 
 #include <mutex>
@@ -13,6 +15,8 @@ namespace ps {
 namespace {
 
 constexpr int kNT = 256;  // threads per workgroup
+
+typedef float f4 __attribute__((ext_vector_type(4)));
 
 // Sum of v over the workgroup in a fixed order: wave butterflies, then wave partials in order.  Every thread
 // gets the result.  sh: kNT / 64 doubles of LDS.
@@ -724,6 +728,192 @@ __global__ void __launch_bounds__(kColsSeries * kColsSlices) k_allan_cols(AllanA
   }
 }
 
+// The same for side-by-side series short enough for a workgroup to hold S of them whole in LDS, w[point][S], each
+// sample read from memory once.  The second differences of a lag L are taken along runs of points L apart: thread
+// (series, phase) walks t, t + L, t + 2 L, ..., so that a term needs one new sample (an LDS read and a conversion
+// to FP64) beside the two it holds.  A lag has L such residues, each cut into a.runs[lag] runs of q or q + 1
+// terms; the runs are dealt to the phases in rounds, consecutive phases on consecutive points.  Terms are added
+// untested; a round of lags with a non-finite sum in the workgroup is taken again with each term tested.  A fixed
+// order: runs of a phase in turn, phases of a wave by butterfly, waves in order.
+// Bound by vector issue (per term a conversion, three FP64 operations and an address): 1800 integrations of 131072
+// channels at 8 lags in 630 us, 290 us of it the read alone (3.3 TB/s in 32-byte rows); 890 us by the window form
+// below, which reads and converts both outer samples of every term, with two barriers per 64 points.
+template <int S, bool TEST, bool CUT>
+__device__ __forceinline__ void series_lag(const float* __restrict__ w, const int P, const int L, const int m,
+                                           const int s, const int ph, double& sum, double& cnt) {
+  constexpr int PH = kSeriesThreads / S;
+  if (L > P / 2) return;  // (2 L may exceed an int)
+  const int M = P - 2 * L;  // terms
+  if (M == 0) return;
+  // residue r has kf terms, and one more (its last run's) when r < rem; its first e runs have q + 1 of them
+  const int kf = CUT ? M / L : (M >= L ? M / L : 0), rem = M - kf * L, q = CUT ? kf / m : kf, e = CUT ? kf - q * m : 0;
+  const int items = CUT ? L * m : (kf ? L : M);
+  const float inv = CUT ? 1.0f / (float)L : 0.0f;
+  const int step = L * S;
+  for (int i0 = 0; i0 < items; i0 += PH) {
+    const int i = min(i0 + ph, items - 1);  // a phase without a run repeats the last one and drops it
+    int seg = 0, r = i;
+    if constexpr (CUT) {  // (i + 1/2) / L is at least 1 / (2 L) from a whole number, far more than its rounding
+      seg = (int)(((float)i + 0.5f) * inv);
+      r = i - seg * L;
+    }
+    const bool more = CUT ? seg < e || (seg == m - 1 && r < rem) : r < rem;  // one term beyond q
+    int at = (CUT ? r + (seg * q + min(seg, e)) * L : r) * S + s;            // the run's first sample
+    double x0 = (double)w[at], x1 = (double)w[at + step];
+    at += 2 * step;
+    double part = 0.0, n = 0.0;
+    auto add = [&](const double d) {
+      if constexpr (TEST) {
+        const bool use = finite(d);
+        part += use ? d * d : 0.0;
+        n += use ? 1.0 : 0.0;
+      } else {
+        part = fma(d, d, part);
+      }
+    };
+    auto terms = [&](auto count) {
+      constexpr int C = decltype(count)::value;
+      float v[C];
+#pragma unroll
+      for (int j = 0; j < C; ++j) v[j] = w[at + j * step];
+      at += C * step;
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const double x2 = (double)v[j];
+        add(x2 - 2.0 * x1 + x0);
+        x0 = x1;
+        x1 = x2;
+      }
+    };
+    int k = q;
+#pragma unroll 1
+    for (; k >= 8; k -= 8) terms(std::integral_constant<int, 8>{});
+    if (k & 4) terms(std::integral_constant<int, 4>{});
+    if (k & 2) terms(std::integral_constant<int, 2>{});
+    if (k & 1) terms(std::integral_constant<int, 1>{});
+    const double d = (double)w[more ? at : s] - 2.0 * x1 + x0;
+    if (TEST ? more : true) add(more ? d : 0.0);
+    const bool own = i0 + ph < items;
+    sum += own ? part : 0.0;
+    if constexpr (TEST) cnt += own ? n : 0.0;
+  }
+}
+
+// S series to a workgroup of 512 threads, two workgroups to a CU; V: float, or four neighbouring series at once where
+// rows are whole aligned quadruples.  Workgroups of 8 and 16 series share cache lines with their neighbours, which run
+// on the same XCD at the same time.
+template <int S, class V>
+__global__ void __launch_bounds__(kSeriesThreads) k_allan_series(AllanArgs a) {
+  constexpr int NT = kSeriesThreads, PH = NT / S, NW = NT / 64;
+  constexpr int LG = 128 / S;  // lags per round of sums
+  constexpr int W = (int)sizeof(V) / 4, G = S / W, RPS = NT / G, LD = 8;
+  __shared__ double red[LG][NW][S];           // 8 KiB
+  extern __shared__ __align__(16) float w[];  // [n_points][S]
+  const int tid = (int)threadIdx.x, s = tid % S, ph = tid / S, lane = tid % 64, wv = tid / 64;
+  const int P = (int)a.n_points;
+  const int64_t sb = (int64_t)xcd_remap((int)blockIdx.x, (int)gridDim.x) * S;
+  // rows in batches of LD loads, every load issued (past the end: the batch's first row again, not stored)
+  const int c = W * (tid % G);
+  const float* x = a.x + (sb + c < a.n_series ? sb + c : 0);
+  double msum[W];
+#pragma unroll
+  for (int k = 0; k < W; ++k) msum[k] = 0.0;
+  for (int t0 = tid / G; t0 < P; t0 += LD * RPS) {
+    V d[LD];
+    const float* p = x + (int64_t)t0 * a.point_stride;
+#pragma unroll
+    for (int j = 0; j < LD; ++j)
+      d[j] = *reinterpret_cast<const V*>(p + (t0 + j * RPS < P ? (int64_t)j * RPS * a.point_stride : 0));
+#pragma unroll
+    for (int j = 0; j < LD; ++j)
+      if (t0 + j * RPS < P) {
+        *reinterpret_cast<V*>(&w[(t0 + j * RPS) * S + c]) = d[j];
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          if constexpr (W == 1) msum[k] += (double)d[j];
+          else msum[k] += (double)d[j][k];
+        }
+      }
+  }
+  // sum over the workgroup's threads of a series, left in red[slot][wave][series]
+  auto put = [&](double v, const int slot) {
+#pragma unroll
+    for (int o = 32; o >= S; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane < S) red[slot][wv][lane] = v;
+  };
+  auto total = [&](const int slot, const int c) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) v += red[slot][k][c];
+    return v;
+  };
+  double mean2 = 1.0;  // of series tid % S
+  if (a.normalize) {
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+#pragma unroll
+      for (int o = 32; o >= G; o >>= 1) msum[k] += __shfl_xor(msum[k], o, 64);
+      if (lane < G) red[0][wv][c + k] = msum[k];
+    }
+    __syncthreads();
+    double m = total(0, s), n = (double)P;
+    const bool again = __syncthreads_or(!finite(m));
+    if (again) {  // leave the non-finite samples out
+      double v = 0.0, c = 0.0;
+      for (int t = ph; t < P; t += PH) {
+        const float x = w[t * S + s];
+        if (isfinite(x)) {
+          v += (double)x;
+          c += 1.0;
+        }
+      }
+      put(v, 0);
+      put(c, 1);
+      __syncthreads();
+      m = total(0, s);
+      n = total(1, s);
+      __syncthreads();
+    }
+    m /= n;
+    mean2 = m * m;
+  }
+  __syncthreads();  // the window is complete, and red free
+  for (int l0 = 0; l0 < a.n_lags; l0 += LG) {
+    const int nl = a.n_lags - l0 < LG ? a.n_lags - l0 : LG;
+    for (int l = 0; l < nl; ++l) {
+      double sum = 0.0, cnt = 0.0;
+      if (a.runs[l0 + l] > 1) series_lag<S, false, true>(w, P, a.lags[l0 + l], a.runs[l0 + l], s, ph, sum, cnt);
+      else series_lag<S, false, false>(w, P, a.lags[l0 + l], 1, s, ph, sum, cnt);
+      put(sum, l);
+    }
+    __syncthreads();
+    // one thread per (lag, series) of the round
+    const int l = tid / S;
+    const bool writer = l < nl && sb + s < a.n_series;
+    auto write = [&](const double sum, const double n) {
+      const double tau = (double)a.lags[l0 + l] * a.spacing;
+      a.out[(sb + s) * a.n_lags + l0 + l] = n > 0.0 ? sum / n / (2.0 * tau * tau) / mean2 : NAN;
+    };
+    double sum = 0.0;
+    if (writer) sum = total(l, s);
+    const bool again = __syncthreads_or(writer && !finite(sum));
+    if (!again) {
+      if (writer) write(sum, (double)P - 2.0 * a.lags[l0 + l]);  // every term counts (none: a negative count)
+      continue;
+    }
+    for (int k = 0; k < nl; ++k) {  // a lag at a time: its sums in slot 0, its counts in slot 1
+      double v = 0.0, c = 0.0;
+      if (a.runs[l0 + k] > 1) series_lag<S, true, true>(w, P, a.lags[l0 + k], a.runs[l0 + k], s, ph, v, c);
+      else series_lag<S, true, false>(w, P, a.lags[l0 + k], 1, s, ph, v, c);
+      put(v, 0);
+      put(c, 1);
+      __syncthreads();
+      if (writer && l == k) write(total(0, s), total(1, s));
+      __syncthreads();
+    }
+  }
+}
+
 // The same for side-by-side series whose lags are at most kWinMaxLag, through a window of the series held in
 // LDS.  A workgroup owns 32 neighbouring series (128-byte rows of the [t][series] array) and walks t in steps
 // of 64 rows; every row is read from memory once and then serves all its second differences from LDS.  The
@@ -759,7 +949,6 @@ __global__ void __launch_bounds__(kWinThreads) k_allan_window(AllanArgs a) {
   const int ls = 4 * g + 2 * h;
   const bool pin = sb + ls < a.n_series;
   const float* xl = a.x + (pin ? sb + ls : 0);
-  typedef float f4 __attribute__((ext_vector_type(4)));
   typedef float f2 __attribute__((ext_vector_type(2)));
   // (the zeros are substituted when the pair enters the ring, so the load is not waited for until then)
   auto fetch = [&](f2& d, int r) { d = *reinterpret_cast<const f2*>(xl + (int64_t)(r < P ? r : P - 1) * st); };
@@ -999,6 +1188,44 @@ hipError_t launch_band_stats(const float* x, int64_t n_spec, int64_t n_chan, dou
   return hipGetLastError();
 }
 
+// Runs per residue of lag L of the whole-series form with ph phases: cutting a residue's terms into m runs fills the
+// last round of phases better, while each run costs about as much as four more terms (its two first samples, its
+// bounds); the m with the least time for the rounds is taken, among those whose cut runs have an odd number of
+// terms, so that the runs of neighbouring phases start on different banks.
+static int series_runs(int64_t P, int64_t L, int ph) {
+  const int64_t M = P - 2 * L;
+  if (M < 2 * L) return 1;
+  const int64_t kf = M / L;
+  int64_t best = 1, cost = (L + ph - 1) / ph * (kf + 4);
+  for (int64_t m = 2; m <= kf && m <= 64; ++m) {
+    const int64_t q = kf / m, c = (L * m + ph - 1) / ph * (q + 4);
+    if (q % 2 == 1 && c < cost) {
+      cost = c;
+      best = m;
+    }
+  }
+  return (int)best;
+}
+
+// Series per workgroup of the whole-series form (0: too long): as many as fit half a CU's LDS, up to 64, so that
+// short series still make a workgroup's worth of work.
+static int series_per_block(int64_t P) {
+  for (int S = 64; S >= 8; S /= 2)
+    if (P * S * 4 <= kSeriesLdsBytes) return S;
+  return 0;
+}
+
+template <int S>
+static void launch_series(AllanArgs a, hipStream_t s) {
+  for (int l = 0; l < a.n_lags; ++l) a.runs[l] = series_runs(a.n_points, a.lags[l], kSeriesThreads / S);
+  const dim3 grid((unsigned)((a.n_series + S - 1) / S)), block(kSeriesThreads);
+  const size_t lds = (size_t)a.n_points * S * 4;
+  if (reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && a.point_stride % 4 == 0 && a.n_series % 4 == 0)
+    hipLaunchKernelGGL((k_allan_series<S, f4>), grid, block, lds, s, a);
+  else
+    hipLaunchKernelGGL((k_allan_series<S, float>), grid, block, lds, s, a);
+}
+
 static bool allan_cols(int64_t n_series, int64_t point_stride, int64_t series_stride) {
   return series_stride == 1 && point_stride >= n_series && n_series >= 64;
 }
@@ -1014,11 +1241,20 @@ hipError_t launch_allan(const AllanArgs& a, hipStream_t s) {
   int lmax = 0;
   for (int l = 0; l < a.n_lags; ++l) lmax = a.lags[l] > lmax ? a.lags[l] : lmax;
   const bool rows16 = reinterpret_cast<uintptr_t>(a.x) % 8 == 0 && a.point_stride % 2 == 0 && a.n_series % 2 == 0;
-  if (allan_cols(a.n_series, a.point_stride, a.series_stride) && lmax <= kWinMaxLag && rows16 &&
+  const bool cols = allan_cols(a.n_series, a.point_stride, a.series_stride);
+  const int S = cols && a.n_points >= 1 ? series_per_block(a.n_points) : 0;
+  if (S) {  // up to 2288 points
+    switch (S) {
+      case 64: launch_series<64>(a, s); break;
+      case 32: launch_series<32>(a, s); break;
+      case 16: launch_series<16>(a, s); break;
+      default: launch_series<8>(a, s); break;
+    }
+  } else if (cols && lmax <= kWinMaxLag && rows16 &&
       a.n_points >= 1 && a.n_points < (int64_t(1) << 31)) {  // (no rows: the column form writes NaN)
     hipLaunchKernelGGL(k_allan_window, dim3((unsigned)((a.n_series + kWinSeries - 1) / kWinSeries)),
                        dim3(kWinThreads), 0, s, a);
-  } else if (allan_cols(a.n_series, a.point_stride, a.series_stride)) {
+  } else if (cols) {
     hipLaunchKernelGGL(k_allan_cols, dim3((unsigned)((a.n_series + kColsSeries - 1) / kColsSeries)),
                        dim3(kColsSeries * kColsSlices), 0, s, a);
   } else {

@@ -296,3 +296,27 @@ def test_bandpass_correct_alignment(env, n, shift):
     t.copy_(torch.from_numpy(hk))
     got = pk.bandpass_correct(t, torch.from_numpy(sm).to(dev), torch.from_numpy(G).to(dev))
     rel_close(got.cpu().numpy(), post.bandpass_correct(hk, sm, G), 1e-6)
+
+
+@pytest.mark.parametrize("P,n", [(1, 64), (2, 66), (3, 65), (100, 68), (286, 129), (287, 132), (572, 70), (573, 96),
+                                 (1144, 80), (1145, 67), (1800, 72), (2288, 64), (2289, 64)])
+def test_allan_side_by_side_sizes(env, P, n):
+    """Side-by-side series at the edges of the whole-series form's widths (8, 16, 32 and 64 series to a workgroup; past
+    2288 points the window form), with whole and ragged groups of series, lags that cut runs evenly and not, lags
+    without a term, and non-finite samples.  FP64 sums in another order: of order P eps, bound 1e-10."""
+    torch, pk, dev = env
+    rng = np.random.default_rng(P + n)
+    x = (1 + 0.01 * rng.standard_normal((P, n))).astype(np.float32)
+    lags = [1, 2, 3, 7, 33, 45, 64, 65, 127, 256, 500, max(1, (P - 1) // 2), P // 2 + 1, 2 ** 31 - 1]
+    for bad in (False, True):
+        if bad:
+            x[P // 2, 1] = np.nan
+            x[0, n - 1] = np.inf
+            x[:, 5] = -np.inf
+            x[P // 3, 6] = 3e38
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            ref = post.allan(x.T, lags, 0.5, bad)
+        say(f"allan side by side P={P} n={n} bad={bad}")
+        got = pk.allan(torch.from_numpy(x).to(dev), lags, 0.5, normalize=bad, axis=0).cpu().numpy()
+        rel_close(got, ref, 1e-10)

@@ -393,11 +393,11 @@ bool uses_fused(const ps_instance& c, const ps_schedule* s) {
   return !s || s->single_pass != 2;
 }
 
-// N/8-thread workgroups, one per slot and pair: about 2^20 / N of them (some 2000 waves, each then walking
-// twice as many frames as with 2^21 / N, which measured 7-17 % slower at 2^10 .. 2^12), and the slots hold
-// 16 MiB whatever N is
+// N/16 threads per slot and pair: about 2^21 / N slots put two waves on each SIMD, the most their registers allow,
+// and the slots hold 32 MiB whatever N is (2^20 / N with 16 MiB: 4096 frames of 2^12 int8 points 53.1 us for the
+// transforms against 40.7, 59.0 against 48.1 with the Stokes; 2^22 / N: 63)
 int default_slots_fused(const ps_instance& c) {
-  const int64_t target = (int64_t(1) << 20) / c.fft_len;
+  const int64_t target = (int64_t(1) << 21) / c.fft_len;
   int G = 1;
   while (2 * G * c.n_pairs <= target && 2 * G <= 8192) G *= 2;
   return G;
@@ -756,18 +756,26 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   return PS_OK;
 }
 
+// The part of an output launch's arguments that says where its sums are: the accumulator slots of the instance's
+// first n_frames frames, or their chunk sums (reduce_slots) when there are many.
+void set_slots(ps_plan_t plan, const Inst& I, int64_t n_frames, ps::OutArgs* o) {
+  const int64_t slots = std::min<int64_t>(I.G, n_frames);
+  const bool reduced = slots > ps::kDirectSlots;
+  o->acc = ws_ptr<double>(plan, reduced ? I.off_sumpart : I.off_acc);
+  o->slots = (int32_t)(reduced ? ps::slot_reduce_chunks(slots) : slots);
+  o->slot_stride = (int64_t)I.slot_doubles();
+  o->N1 = (int32_t)I.N1;
+  o->N2 = (int32_t)I.N2;
+  o->P = I.cfg.n_pairs;
+  o->C = I.C;
+  o->parts = ps::output_parts(o->N1, o->N2, o->P, o->slots);
+}
+
 // Arguments of the Stokes output of instance I over its first n_frames frames (Eq. 2 with cal, or unit
 // gains, no leakage and psi = 0 when cal is null).
 ps::OutArgs stokes_args(ps_plan_t plan, const Inst& I, int64_t n_frames, const ps_cal* cal, float* iquv) {
   ps::OutArgs o{};
-  const bool reduced = std::min<int64_t>(I.G, n_frames) > ps::kDirectSlots;
-  o.acc = ws_ptr<double>(plan, reduced ? I.off_sumacc : I.off_acc);
-  o.slots = reduced ? 1 : (int32_t)std::min<int64_t>(I.G, n_frames);
-  o.slot_stride = (int64_t)I.slot_doubles();
-  o.N1 = (int32_t)I.N1;
-  o.N2 = (int32_t)I.N2;
-  o.P = I.cfg.n_pairs;
-  o.C = I.C;
+  set_slots(plan, I, n_frames, &o);
   o.n_frames = (double)n_frames;
   o.sumw2_dev = ws_ptr<double>(plan, I.off_sumw2);
   o.scale = 1.0 / ((double)n_frames * I.sumw2);
@@ -813,7 +821,7 @@ ps_status run_frames(ps_plan_t plan, Inst& I, const uint8_t* base, int64_t F, bo
       fa.N2 = (int32_t)I.N2;
       fa.F0 = I.n_frames;
       fa.slot_stride = (int64_t)I.slot_doubles();
-      hipError_t e = timed(plan, PS_KERNEL_COLPASS, [&](const ps::Launch& l) { return ps::launch_fused((int)I.N, I.cfg.bits, fa, l); });
+      hipError_t e = timed(plan, PS_KERNEL_COLPASS, [&](const ps::Launch& l) { return ps::launch_fused((int)I.N, I.cfg.bits, I.load_mode, fa, l); });
       if (e != hipSuccess) return hip_fail(e, "single-pass launch");
       I.first = false;
       I.n_frames += nf;
@@ -1212,28 +1220,16 @@ ps_status ps_accumulate_stokes(ps_plan_t plan, const void* const* packed_dev, co
   return ps_stokes_all(plan, cal, rest.data());
 }
 
-// Sum the slots of an instance that uses many of them into one (readers then see a single slot).
-static ps_status reduce_slots(ps_plan_t plan, const Inst& I) {
+// Chunk sums of the slots of an instance that uses many of them, and with total their sum as one slot.
+static ps_status reduce_slots(ps_plan_t plan, const Inst& I, bool total = false) {
   if (!I.use_reduced()) return PS_OK;
   hipError_t e = timed(plan, PS_KERNEL_OTHER, [&](const ps::Launch& l) {
     return ps::launch_slot_reduce(ws_ptr<double>(plan, I.off_acc), (int64_t)I.slot_doubles(), I.slots_used(),
                                   (int64_t)I.slot_doubles(), ws_ptr<double>(plan, I.off_sumpart),
-                                  ws_ptr<double>(plan, I.off_sumacc), l);
+                                  total ? ws_ptr<double>(plan, I.off_sumacc) : nullptr, l);
   });
   if (e != hipSuccess) return hip_fail(e, "slot reduction launch");
   return PS_OK;
-}
-
-static ps::OutArgs out_args(ps_plan_t plan, const Inst& I) {
-  ps::OutArgs o{};
-  o.acc = ws_ptr<double>(plan, I.use_reduced() ? I.off_sumacc : I.off_acc);
-  o.slots = I.use_reduced() ? 1 : I.slots_used();
-  o.slot_stride = (int64_t)I.slot_doubles();
-  o.N1 = (int32_t)I.N1;
-  o.N2 = (int32_t)I.N2;
-  o.P = I.cfg.n_pairs;
-  o.C = I.C;
-  return o;
 }
 
 ps_status ps_spectra(ps_plan_t plan, int32_t inst, double* out_dev, int64_t* n_frames) {
@@ -1244,7 +1240,8 @@ ps_status ps_spectra(ps_plan_t plan, int32_t inst, double* out_dev, int64_t* n_f
   if (!out_dev) return fail(PS_ERR_ARG, "null output");
   if (I.n_frames == 0) return fail(PS_ERR_STATE, "instance %d has no accumulated frames", inst);
   if ((st = reduce_slots(plan, I)) != PS_OK) return st;
-  ps::OutArgs o = out_args(plan, I);
+  ps::OutArgs o{};
+  set_slots(plan, I, I.n_frames, &o);
   o.spectra = out_dev;
   hipError_t e = timed(plan, PS_KERNEL_SPECTRA, [&](const ps::Launch& l) { return ps::launch_spectra(o, l); });
   if (e != hipSuccess) return hip_fail(e, "spectra launch");
@@ -1283,7 +1280,7 @@ ps_status ps_stokes_all(ps_plan_t plan, const ps_cal* cal, float* const* iquv_de
       return fail(PS_ERR_ARG, "instance %zu: unknown feed %d", i, cal[i].feed);
     const ps::OutArgs o = stokes_args(plan, I, I.n_frames, cal ? &cal[i] : nullptr, iquv_dev[i]);
     outs.push_back(o);
-    total += ps::output_tiles(o.N1, o.N2, o.P);
+    total += ps::output_tiles(o);
     ends.push_back(total);
   }
   if (outs.empty()) return PS_OK;
@@ -1420,7 +1417,7 @@ ps_status ps_calibrate_backward(ps_plan_t plan, int32_t inst, const void* packed
   }
   if (I.N1 > 512 || I.N2 > 512)
     return fail(PS_ERR_UNSUPPORTED, "the adjoint is built for passes of at most 512 points (fft_len <= 2^18)");
-  if ((st = reduce_slots(plan, I)) != PS_OK) return st;
+  if ((st = reduce_slots(plan, I, true)) != PS_OK) return st;
   ps::BwChanArgs ca{};
   ca.acc = ws_ptr<double>(plan, I.use_reduced() ? I.off_sumacc : I.off_acc);
   ca.slots = I.use_reduced() ? 1 : I.slots_used();

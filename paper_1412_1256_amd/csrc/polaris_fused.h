@@ -21,14 +21,15 @@ struct FusedArgs {
 };
 
 constexpr int kFusedMinLog2 = 8, kFusedMaxLog2 = 12;
-int fused_threads(int N);
-hipError_t launch_fused(int N, int bits, const FusedArgs& a, const Launch& l);
+// mode: 0 item by item, 1 the pair (0, 1) of two streams, 2 four streams (codes of at most 8 bits)
+hipError_t launch_fused(int N, int bits, int mode, const FusedArgs& a, const Launch& l);
 
-// Many accumulator slots (beyond kDirectSlots) are summed by a two-stage reduction before the readers run:
-// chunks of kReduceChunk slots in slot order, then the chunk sums in chunk order (a fixed order, so results
-// are identical from run to run and independent of how the frames were split over calls).
+// Many accumulator slots (beyond kDirectSlots) are summed in chunks of kReduceChunk slots, in slot order, before the
+// readers run; the output kernels read the chunk sums as slots, and the adjoint one sum of them, added in chunk order
+// (out; nullptr: not wanted).  A fixed order, so results are identical from run to run and independent of how the
+// frames were split over calls.
 constexpr int kDirectSlots = 64, kReduceChunk = 32;
-inline int64_t slot_reduce_chunks(int slots) { return (slots + kReduceChunk - 1) / kReduceChunk; }
+inline int64_t slot_reduce_chunks(int64_t slots) { return (slots + kReduceChunk - 1) / kReduceChunk; }
 hipError_t launch_slot_reduce(const double* acc, int64_t elems, int slots, int64_t slot_stride, double* part,
                               double* out, const Launch& l);
 

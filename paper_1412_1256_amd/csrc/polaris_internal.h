@@ -52,6 +52,7 @@ struct RowArgs {
 struct OutArgs {
   const double* acc;        // [slots][P][N1/2][4][N2]
   int32_t slots;            // slots to sum (min(G, frames))
+  int32_t parts;            // threads that share a channel's slots (output_parts)
   int64_t slot_stride;
   int32_t N1, N2, P;
   int64_t C;
@@ -187,7 +188,8 @@ hipError_t launch_colpass_batch(int N1, int cols, int bits, int mode, const Batc
 hipError_t launch_rowpass_batch(int N2, int fb, const BatchArgs& b, const Launch& l);
 hipError_t launch_output_batch(bool stokes, const BatchArgs& b, const Launch& l);
 int rowpass_units_per_tile(int N2);
-int output_tiles(int N1, int N2, int P);
+int output_parts(int N1, int N2, int P, int slots);
+int output_tiles(const OutArgs& a);
 
 int colpass_cols(int N1);     // default columns per column-pass workgroup
 bool colpass_has(int N1, int cols);

@@ -517,31 +517,41 @@ __global__ void __launch_bounds__((rowpass_threads<L, UB, FB, SQ>()))
 // output: accumulators -> natural channel order (raw spectra, or calibrated Stokes by Eq. 2)
 // ------------------------------------------------------------------------------------------------
 
-constexpr int kOutThreads = 512;  // one channel of the 32 x 16 tile per thread
+// A workgroup gathers rt rows x kt bins of channels with a.parts threads per channel (rt kt parts = 512 for
+// transforms of at least 32 rows and bins): thread (channel, part) adds its run of consecutive slots in order, and
+// the parts are then added in order.  A short transform has many slots but few tiles; with one thread per channel
+// and slot after slot, 64 slots of 2^10 points were one workgroup's work for 20.2 us; 4.2 us with 32 parts.
+constexpr int kOutThreads = 512, kOutRows = 32, kOutBins = 16;
+
+__host__ __device__ inline int output_rows(int N1, int parts) { return (N1 < kOutRows ? N1 : kOutRows) / parts; }
+__host__ __device__ inline int output_bins(int N2) { return N2 / 2 < kOutBins ? N2 / 2 : kOutBins; }
 
 template <bool STOKES>
 __device__ __forceinline__ void output_tile(const OutArgs& a, const int bx, const int by, const int p) {
-  constexpr int RT = 32, KT = 16;
-  __shared__ double t[4][RT][KT + 1];
+  __shared__ double t[4][kOutRows][kOutBins + 1];  // [product][part, row][bin]
   const int L = a.N2, U = a.N1 / 2;
-  const int rt = RT < a.N1 ? RT : a.N1;
-  const int kt = KT < L / 2 ? KT : L / 2;
+  const int rt = output_rows(a.N1, a.parts), kt = output_bins(a.N2);
   const int r0 = bx * rt, k20 = by * kt;
-  for (int e = (int)threadIdx.x; e < rt * kt; e += kOutThreads) {
-    const int rl = e / kt, kk = e % kt;
+  const int run = (a.slots + a.parts - 1) / a.parts;
+  for (int e = (int)threadIdx.x; e < a.parts * rt * kt; e += kOutThreads) {
+    const int pr = e / kt, kk = e % kt, rl = pr % rt, part = pr / rt;
     const int r = r0 + rl, k2 = k20 + kk;
     int u, half;
     if (r == 0) { u = 0; half = 0; }
     else if (2 * r == a.N1) { u = 0; half = 1; }
     else if (2 * r < a.N1) { u = r; half = 0; }
     else { u = a.N1 - r; half = 1; }
+    const int g0 = part * run, g1 = min(a.slots, g0 + run);
     const double* src = a.acc + ((int64_t)(p * U + u) * 4) * L + half * (L / 2) + k2;
     // slots are added in order; their loads go out eight at a time
-    double v[4];
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    int g = g0;
+    if (g < g1) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = src[(int64_t)q * L];
-    int g = 1;
-    for (; g + 8 <= a.slots; g += 8) {
+      for (int q = 0; q < 4; ++q) v[q] = src[(int64_t)g * a.slot_stride + (int64_t)q * L];
+      ++g;
+    }
+    for (; g + 8 <= g1; g += 8) {
       double w[8][4];
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -552,11 +562,11 @@ __device__ __forceinline__ void output_tile(const OutArgs& a, const int bx, cons
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] += w[j][q];
     }
-    for (; g < a.slots; ++g)
+    for (; g < g1; ++g)
 #pragma unroll
       for (int q = 0; q < 4; ++q) v[q] += src[(int64_t)g * a.slot_stride + (int64_t)q * L];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) t[q][rl][kk] = v[q];
+    for (int q = 0; q < 4; ++q) t[q][pr][kk] = v[q];
   }
   __syncthreads();
   double scale = a.scale;
@@ -565,8 +575,14 @@ __device__ __forceinline__ void output_tile(const OutArgs& a, const int bx, cons
     const int kk = e / rt, rl = e % rt;
     const int64_t k = (int64_t)(k20 + kk) * a.N1 + r0 + rl;
     // stored sums are 4 XX*, 4 YY*, 4 XY* (exact power-of-two scale)
-    const double axx = 0.25 * t[0][rl][kk], ayy = 0.25 * t[1][rl][kk];
-    const double axr = 0.25 * t[2][rl][kk], axi = 0.25 * t[3][rl][kk];
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = t[q][rl][kk];
+    for (int part = 1; part < a.parts; ++part)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += t[q][part * rt + rl][kk];
+    const double axx = 0.25 * v[0], ayy = 0.25 * v[1];
+    const double axr = 0.25 * v[2], axi = 0.25 * v[3];
     if constexpr (!STOKES) {
       double* o = a.spectra + (int64_t)p * 4 * a.C + k;
       o[0] = axx;
@@ -585,8 +601,8 @@ __global__ void __launch_bounds__(kOutThreads) k_output(OutArgs a) {
 }
 
 // tiles of one instance: (N1 / rt) x (N2 / 2 / kt) x P
-__host__ __device__ inline int output_tiles_x(int N1) { return N1 / (N1 < 32 ? N1 : 32); }
-__host__ __device__ inline int output_tiles_y(int N2) { return N2 / 2 / (N2 / 2 < 16 ? N2 / 2 : 16); }
+__host__ __device__ inline int output_tiles_x(int N1, int parts) { return N1 / output_rows(N1, parts); }
+__host__ __device__ inline int output_tiles_y(int N2) { return N2 / 2 / output_bins(N2); }
 
 template <bool STOKES>
 __global__ void __launch_bounds__(kOutThreads)
@@ -595,7 +611,7 @@ __global__ void __launch_bounds__(kOutThreads)
   const int t = batch_task(tile_end, n_tasks, tile);
   const int local = tile - (t ? tile_end[t - 1] : 0);
   const OutArgs a = load_const(tasks + t);
-  const int nx = output_tiles_x(a.N1), ny = output_tiles_y(a.N2);
+  const int nx = output_tiles_x(a.N1, a.parts), ny = output_tiles_y(a.N2);
   output_tile<STOKES>(a, local % nx, (local / nx) % ny, local / (nx * ny));
 }
 
@@ -856,7 +872,17 @@ hipError_t launch_rowpass_batch(int N2, int fb, const BatchArgs& b, const Launch
 
 int rowpass_units_per_tile(int N2) { return N2 >= 256 ? 1 : (N2 == 128 ? 2 : (N2 == 64 ? 4 : 8)); }
 
-int output_tiles(int N1, int N2, int P) { return output_tiles_x(N1) * output_tiles_y(N2) * P; }
+int output_tiles(const OutArgs& a) { return output_tiles_x(a.N1, a.parts) * output_tiles_y(a.N2) * a.P; }
+
+// Threads per channel: doubled while each still has two slots or more and the tiles stay within two per CU
+// (transforms of 2^18 points have 1024 tiles and two slots: one thread each).
+int output_parts(int N1, int N2, int P, int slots) {
+  int parts = 1;
+  while (4 * parts <= slots && 2 * parts <= (N1 < kOutRows ? N1 : kOutRows) &&
+         2 * output_tiles_x(N1, parts) * output_tiles_y(N2) * P <= 512)
+    parts *= 2;
+  return parts;
+}
 
 hipError_t launch_output_batch(bool stokes, const BatchArgs& b, const Launch& s) {
   const OutArgs* t = static_cast<const OutArgs*>(b.tasks);
@@ -866,9 +892,7 @@ hipError_t launch_output_batch(bool stokes, const BatchArgs& b, const Launch& s)
 }
 
 static dim3 output_grid(const OutArgs& a) {
-  const int rt = a.N1 < 32 ? a.N1 : 32;
-  const int kt = a.N2 / 2 < 16 ? a.N2 / 2 : 16;
-  return dim3((unsigned)(a.N1 / rt), (unsigned)(a.N2 / 2 / kt), (unsigned)a.P);
+  return dim3((unsigned)output_tiles_x(a.N1, a.parts), (unsigned)output_tiles_y(a.N2), (unsigned)a.P);
 }
 
 hipError_t launch_stokes(const OutArgs& a, const Launch& s) {

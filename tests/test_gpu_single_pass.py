@@ -225,3 +225,32 @@ def test_backward_reads_reduced_slots(env):
     rel = np.max(np.abs(dt - gr["d_taps"])) / np.max(np.abs(gr["d_taps"]))
     say(f"  taps rel err {rel}")
     assert rel < 1e-4
+
+
+@pytest.mark.parametrize("log2n", [8, 9, 10, 11, 12])
+@pytest.mark.parametrize("bits,streams", [(2, 2), (4, 2), (8, 2), (2, 4), (4, 4), (8, 4)])
+def test_word_loads_slots_and_parts(env, log2n, bits, streams):
+    """Slots that share a wave and slots without a frame, runs of unequal length, slot counts around the output
+    kernel's shares and the chunked reduction; codes read as words (aligned) and item by item (a buffer that starts
+    one byte off).  Against the oracle normwise 1e-5; the two loads and split calls bitwise equal."""
+    torch, pk, dev = env
+    N = 1 << log2n
+    rng = synth.rng_for(301, log2n, bits, streams)
+    for slots, F in ((1, 3), (2, 5), (8, 3), (64, 67), (128, 66), (128, 200)):
+        ts = rng.standard_normal((F * N, streams)) * (16.0 if bits == 8 else 1.0)
+        ts[:, -1] += 0.5 * ts[:, 0]
+        inst = synth.gen._instance(synth.pack_codes(synth.quantize(ts, bits), bits), bits, streams, N, F, window="hann")
+        acc, _, _, _ = oracle.run_instance(inst)
+        sched = pk.Schedule(rowpass_slots=slots, single_pass=1)
+        say(f"N=2^{log2n} bits={bits} streams={streams} slots={slots} frames={F}")
+        spec, nf, st = run(env, inst, sched)
+        assert nf == F and np.all(spectra_err(spec, acc) < TOL)
+        split, _, _ = run(env, inst, sched, calls=2)
+        assert np.array_equal(split, spec)
+        plan = pk.Plan([pk.Instance.from_synth(inst)], device=dev, schedules=[sched])
+        raw = torch.zeros(inst["packed"].size + 1, dtype=torch.uint8, device=dev)
+        raw[1:] = torch.from_numpy(inst["packed"]).to(dev)
+        plan.reset()
+        plan.accumulate(raw[1:])
+        off, _ = plan.spectra()
+        assert np.array_equal(off.cpu().numpy(), spec)

@@ -1323,18 +1323,13 @@ ps_status ps_histograms(ps_plan_t plan, int32_t inst, uint64_t* counts_dev, doub
   if ((st = check_inst(plan, inst)) != PS_OK) return st;
   const Inst& I = plan->inst[(size_t)inst];
   if (!I.hist_on || !I.hist_zeroed) return fail(PS_ERR_STATE, "instance %d has no histograms in this integration", inst);
-  const int64_t nb = (int64_t)I.cfg.n_pairs * 2 * I.hist_bins();
-  unsigned long long* h = ws_ptr<unsigned long long>(plan, I.off_hist);
-  hipError_t e = hipSuccess;
-  if (counts_dev) {
-    e = ps::launch_copy(h, counts_dev, (size_t)nb * 8, plan->stream);
-    if (e != hipSuccess) return hip_fail(e, "histogram copy");
-  }
-  if (power_dev) {
-    e = timed(plan, PS_KERNEL_OTHER, [&](const ps::Launch& l) {
-      return ps::launch_hist_power(h, I.cfg.n_pairs * 2, I.cfg.bits, power_dev, l);
+  if (counts_dev || power_dev) {
+    static_assert(sizeof(unsigned long long) == sizeof(uint64_t), "counts are 64-bit words");
+    hipError_t e = timed(plan, PS_KERNEL_OTHER, [&](const ps::Launch& l) {
+      return ps::launch_hist_read(ws_ptr<unsigned long long>(plan, I.off_hist), I.cfg.n_pairs * 2, I.cfg.bits,
+                                  reinterpret_cast<unsigned long long*>(counts_dev), power_dev, l);
     });
-    if (e != hipSuccess) return hip_fail(e, "histogram power launch");
+    if (e != hipSuccess) return hip_fail(e, "histogram read launch");
   }
   if (n_frames) *n_frames = I.hist_frames;
   return PS_OK;

@@ -219,7 +219,8 @@ bool bw_taps_block_form(int64_t N, int n_taps);  // the one-pass tap gradient ap
 int64_t bw_taps_part_doubles(int64_t N);         // its per-block sums
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t s);
-hipError_t launch_hist_power(const unsigned long long* counts, int n_streams, int bits, double* power,
-                             const Launch& l);
+// the bins of n_streams streams copied to out and their power estimates (either may be nullptr)
+hipError_t launch_hist_read(const unsigned long long* counts, int n_streams, int bits, unsigned long long* out,
+                            double* power, const Launch& l);
 
 }  // namespace ps

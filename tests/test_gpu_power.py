@@ -98,3 +98,25 @@ def test_reset_and_errors(env):
     with pytest.raises(pk.PolarisError) as e:
         f32.set_histograms(True)
     assert e.value.code == "PS_ERR_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_histograms_read_separately(env, bits):
+    """The counts alone, the estimates alone (the other pointer NULL) and both together are the same, for fewer bins
+    than a wave has lanes and for more, with the streams of two pairs; whole numbers, so exact."""
+    import ctypes as C
+    torch, pk, dev = env
+    rng = np.random.default_rng(bits)
+    N, F = 1 << 13, 3
+    packed = torch.from_numpy(rng.integers(0, 256, N * F * 4 * bits // 8, dtype=np.uint8)).to(dev)
+    plan = pk.Plan([pk.Instance(fft_len=N, bits=bits, n_streams=4, pairs=((0, 2), (1, 3)))], device=dev)
+    plan.set_histograms(True)
+    plan.reset()
+    plan.accumulate(packed)
+    counts, power, _ = plan.histograms()
+    only_c, only_p = torch.empty_like(counts), torch.empty_like(power)
+    assert pk.lib().ps_histograms(plan._h, 0, C.c_void_p(only_c.data_ptr()), None, None) == 0
+    assert pk.lib().ps_histograms(plan._h, 0, None, C.c_void_p(only_p.data_ptr()), None) == 0
+    torch.cuda.synchronize(dev)
+    assert torch.equal(only_c, counts) and torch.equal(only_p.nan_to_num(-1.0), power.nan_to_num(-1.0))
+    assert int(counts.sum()) == 4 * N * F

@@ -144,23 +144,28 @@ __device__ __forceinline__ void colpass_tile(const ColArgs& a, const int blk) {
       for (int r = 0; r < R0; ++r)
         if (pin<L, R0>(ts, i, r) < a.hist_rows) hrows |= 1u << (i * R0 + r);
   }
+  // The window of this thread's samples, the same for every frame, stays in registers (16 more of the 256 that two
+  // waves per SIMD leave).  Read from L2 in every frame, half as many bytes as the intermediate, it made half-
+  // overlapped frames of 2^18 points with a Hamming window 136 us per second against 128.
+  float win[V][8];
+  if (a.win) {
+#pragma unroll
+    for (int i = 0; i < 8 / R0; ++i)
+#pragma unroll
+      for (int r = 0; r < R0; ++r)
+#pragma unroll
+        for (int c = 0; c < V; ++c) win[c][i * R0 + r] = a.win[(int64_t)pin<L, R0>(ts, i, r) * a.N2 + n2b + c];
+  }
   // input words are fetched one frame ahead of their use
   auto frame = [&](ColLoader<BITS, FAST, V>& ld, const int f) {
     float2 v[V][8];
     ld.template convert<L, R0>(v, a, ts, n2b, sx, sy);
     if constexpr (H) hist.count(hs, v, hrows);
-    if (a.win) {  // the window is the same for every frame (and cached in L2); read before the prefetch
+    if (a.win) {
 #pragma unroll
-      for (int i = 0; i < 8 / R0; ++i)
+      for (int c = 0; c < V; ++c)
 #pragma unroll
-        for (int r = 0; r < R0; ++r) {
-          const int64_t n = (int64_t)pin<L, R0>(ts, i, r) * a.N2 + n2b;
-#pragma unroll
-          for (int c = 0; c < V; ++c) {
-            const float w = a.win[n + c];
-            v[c][i * R0 + r] = make_float2(v[c][i * R0 + r].x * w, v[c][i * R0 + r].y * w);
-          }
-        }
+        for (int e = 0; e < 8; ++e) v[c][e] = make_float2(v[c][e].x * win[c][e], v[c][e].y * win[c][e]);
     }
     // The next frame's loads and this frame's stores are issued at raised wave priority, so that they reach
     // the memory system before the other waves' arithmetic (column pass 41.3 -> 40.4 us, two integrations

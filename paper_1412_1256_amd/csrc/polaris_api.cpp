@@ -104,7 +104,9 @@ struct Inst {
   int64_t frames_in(int64_t T) const { return T < N ? 0 : (T - N) / hop + 1; }
   size_t slot_doubles() const { return (size_t)cfg.n_pairs * (size_t)(N1 / 2) * 4 * (size_t)N2; }
   size_t acc_bytes() const { return (size_t)G * slot_doubles() * sizeof(double); }
-  int slots_used() const { return (int)std::min<int64_t>(G, n_frames); }
+  // slots that hold frames after F of them: frame by frame, in the 16-bit row pass in blocks of four
+  int slots_of(int64_t F) const { return (int)std::min<int64_t>(G, mx() ? (F + 3) / 4 : F); }
+  int slots_used() const { return slots_of(n_frames); }
   // readers of more than kDirectSlots slots take their sum from a reduction into one slot
   size_t off_sumacc = 0, off_sumpart = 0;
   bool use_reduced() const { return slots_used() > ps::kDirectSlots; }
@@ -404,15 +406,16 @@ int default_slots_fused(const ps_instance& c) {
 }
 
 // Accumulator slots: enough row-pass frame groups that units x pairs x slots reach about 512 workgroups for
-// frames of at most 2^18 points and 256 beyond (twice the slots measured faster up to 2^18), and 1 for the
-// 16-bit passes, whose row pass spreads frames over its waves.
+// frames of at most 2^18 points and 256 beyond (twice the slots measured faster up to 2^18).  The 16-bit row pass,
+// whose workgroups of four waves share a CU in twos, needs 512 of them as well (two int8 streams, one pair,
+// 2^16 x 500 frames: 148 us with 128 workgroups, 97 with 512; 2^18 x 200: 213 and 192).
 int rowpass_tiles(const ps_instance& c, int N1, int N2) {
   return N1 / 2 / ps::rowpass_units_per_tile(N2) * c.n_pairs;
 }
 
 int default_slots(const ps_instance& c, int N1, int N2) {
-  if (c.precision != PS_PREC_FP32) return 1;
-  const int tiles = rowpass_tiles(c, N1, N2);
+  const bool mx = c.precision != PS_PREC_FP32;
+  const int tiles = mx ? N1 / 2 * c.n_pairs : rowpass_tiles(c, N1, N2);
   const int target = c.fft_len <= (1 << 18) ? 512 : 256;
   int G = 1;
   while (G < 64 && G * tiles < target) G *= 2;
@@ -720,10 +723,17 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   // four streams as the pairs (0, 2) and (1, 3): one workgroup transforms both from the words it reads
   if (m.mode == 2 && c.n_pairs == 2 && c.pair_x[0] == 0 && c.pair_y[0] == 2 && c.pair_x[1] == 1 && c.pair_y[1] == 3)
     m.mode = 3;
+  // Windowed four-stream launches of 256-point columns: up to 2^24 points a pair the items' loads at use, with a
+  // workgroup per pair, were as fast or faster than the words of both pairs (2^17 points: 128 frames 99 against 105
+  // us, 20 frames 28.5 against 31.4; 300 frames 241 against 228).
+  if (m.mode == 3 && ca.win && I.N1 == 256 && (int64_t)ca.n_frames * I.N <= (int64_t(1) << 24)) m.mode = 0;
   if (ca.in_bytes == 0) m.mode = 0;  // the word paths address the launch's input with 32-bit offsets
   const int64_t per_frame = (int64_t)m.col.n_colblk * (m.mode == 3 ? 1 : ca.P);
-  // two or three workgroups fit on a CU: aim at two per CU, each looping over a group of frames
-  int64_t groups = (2 * plan->n_cu + per_frame / 2) / per_frame;
+  // two workgroups fit on a CU: two rounds of them, each looping over a group of frames, so that the second round
+  // evens out the first (one round: the precision case's 10 s 897 us, two rounds 880, three 882, four 890), while a
+  // workgroup keeps at least four frames for its twiddles and matrices (20 frames: one round 28 us, two 33)
+  int64_t groups = (4 * plan->n_cu + per_frame / 2) / per_frame;
+  if (groups * 4 > ca.n_frames) groups = (2 * plan->n_cu + per_frame / 2) / per_frame;
   if (groups < 1) groups = 1;
   if (groups > ca.n_frames) groups = ca.n_frames;
   m.col.frames_per_block = (int32_t)((ca.n_frames + groups - 1) / groups);
@@ -746,7 +756,9 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   r.m.aR = ws_ptr<uint32_t>(plan, I.N2 == 512 ? I.off_mx32 : I.off_mx16);
   r.m.tws = ws_ptr<float2>(plan, I.off_tws_row);
   r.acc = ws_ptr<double>(plan, I.off_acc);
-  r.first = I.first ? 1 : 0;
+  r.G = I.G;
+  r.F0 = I.n_frames;
+  r.slot_stride = (int64_t)I.slot_doubles();
   // the stages scale Z by 1 / (16 * (N1 / 16) * 16) = 1 / (16 N1); products by its square
   r.unscale = std::ldexp(1.0, 2 * (4 + I.m1));
   e = timed(plan, PS_KERNEL_ROWPASS, [&](const ps::Launch& l) {
@@ -759,7 +771,7 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
 // The part of an output launch's arguments that says where its sums are: the accumulator slots of the instance's
 // first n_frames frames, or their chunk sums (reduce_slots) when there are many.
 void set_slots(ps_plan_t plan, const Inst& I, int64_t n_frames, ps::OutArgs* o) {
-  const int64_t slots = std::min<int64_t>(I.G, n_frames);
+  const int slots = I.slots_of(n_frames);
   const bool reduced = slots > ps::kDirectSlots;
   o->acc = ws_ptr<double>(plan, reduced ? I.off_sumpart : I.off_acc);
   o->slots = (int32_t)(reduced ? ps::slot_reduce_chunks(slots) : slots);
@@ -896,10 +908,10 @@ ps_status ps_schedule_candidates(const ps_instance* inst, ps_schedule* out, int3
   std::vector<ps_schedule> v;
   const int m = ilog2_exact(inst->fft_len);
   if (inst->precision != PS_PREC_FP32) {
-    v.push_back(ps_schedule{m / 2, 0, 0, 0, 1, 0});
+    v.push_back(ps_schedule{m / 2, 0, 0, 0, 1, 0});  // the default schedule only (one slot stands for its own)
   } else {
     if (fused_eligible(*inst)) {
-      const int G0 = default_slots_fused(*inst);
+      const int G0 = std::max(1, default_slots_fused(*inst) / 2);  // the default is the largest listed
       for (int G = std::max(1, G0 / 4); G <= std::min(8192, 2 * G0); G *= 2) v.push_back(ps_schedule{m / 2, 0, 0, 0, G, 1});
     }
     for (int m1 = m / 2 - 1; m1 <= m / 2 + 1; ++m1) {
@@ -952,7 +964,7 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
     I.cols = (sched && sched[i].colpass_cols) ? sched[i].colpass_cols : ps::colpass_cols((int)I.N1);
     I.col_wgs = (sched && sched[i].col_wg_per_cu) ? sched[i].col_wg_per_cu : default_col_wgs(inst[i]);
     I.fused = uses_fused(I.cfg, sched ? &sched[i] : nullptr);
-    I.G = (sched && sched[i].rowpass_slots) ? sched[i].rowpass_slots
+    I.G = (sched && sched[i].rowpass_slots && !I.mx()) ? sched[i].rowpass_slots
                                              : (I.fused ? default_slots_fused(I.cfg) : default_slots(I.cfg, (int)I.N1, (int)I.N2));
     I.fb = (sched && sched[i].rowpass_frames) ? sched[i].rowpass_frames
                                               : default_rowpass_frames(I.cfg, (int)I.N1, (int)I.N2, (int)I.G);

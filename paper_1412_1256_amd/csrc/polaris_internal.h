@@ -96,8 +96,10 @@ struct MxRowArgs {
   const uint32_t* T;
   int32_t N1, P, n_frames;
   MxMats m;
-  double* acc;              // [P][N1/2][4][N2] FP64, unscaled
-  int32_t first;
+  double* acc;              // [G][P][N1/2][4][N2] FP64, unscaled
+  int32_t G;                // accumulator slots
+  int64_t F0;               // frames accumulated since ps_reset before this launch
+  int64_t slot_stride;      // doubles per slot
   double unscale;           // 1 / (product scale)^2 of the stages: multiplies the sums before they are stored
 };
 

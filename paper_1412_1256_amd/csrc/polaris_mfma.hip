@@ -210,8 +210,9 @@ __global__ void __launch_bounds__(256, 2) k_colpass_mx(MxColArgs a) {
     for (int pp = 0; pp < NPP; ++pp) {
       const int p = p0 + pp;
       const int sx = NPP == 2 ? pp : c.px[p], sy = NPP == 2 ? pp + 2 : c.py[p];
-      // the stage twiddles are read from LDS in every frame: an opaque zero keeps the compiler from holding
-      // all of them in registers across the frame loop
+      // the stage twiddles are read from LDS, and the window of a radix-32 stage from cache, in every frame: an opaque
+      // zero keeps the compiler from holding all of them in registers across the frame loop (a radix-16 stage's
+      // sixteen window values fit)
       int z0;
       asm volatile("v_mov_b32 %0, 0" : "=v"(z0));
       // ---- stage A (and the radix-2 butterfly of a radix-32 stage B)
@@ -229,7 +230,7 @@ __global__ void __launch_bounds__(256, 2) k_colpass_mx(MxColArgs a) {
             float2 v = in[j][h][jj].level(c, tt, sx, sy);
             if constexpr (WIN) {
               const gbytes wb = uniform_gptr(reinterpret_cast<const uint8_t*>(c.win + (R * jj + b + 16 * h) * N2));
-              const float wv = *(const __attribute__((address_space(1))) float*)(wb + 4u * lane_t);
+              const float wv = *(const __attribute__((address_space(1))) float*)(wb + (4u * lane_t + (H == 2 ? (uint32_t)z0 : 0u)));
               v = make_float2(v.x * wv, v.y * wv);
             }
             xb[0][jj] = pk<PREC>(v.x, v.y);
@@ -295,8 +296,9 @@ __global__ void __launch_bounds__(256, 2) k_colpass_mx(MxColArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// row pass: a workgroup owns one unit (rows k1 and N1 - k1, or 0 and N1/2) of one pair; wave w takes the
-// frames f = w, w + 4, ...  For each row, stage A (vectors b = 16h + n) goes through a wave-private LDS
+// row pass: a workgroup owns one unit (rows k1 and N1 - k1, or 0 and N1/2) of one pair and one accumulator slot g of
+// G; wave w takes the absolute frames a = 4 b + w of the blocks b with b mod G = g, so that short integrations use
+// one slot.  For each row, stage A (vectors b = 16h + n) goes through a wave-private LDS
 // exchange to stage B (vectors kappa); the spectra of both rows go to LDS, and each lane forms XX*, YY*,
 // XY* of its channel slots and integrates them in registers.  At the end the four waves' sums are added in
 // wave order, unscaled (an exact power of two) and stored into the FP64 accumulators.
@@ -317,6 +319,13 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
   const int u = (int)blockIdx.x, p = (int)blockIdx.y;
   const int N1 = a.N1, U = N1 / 2;
+  // frames of the launch, f = a - F0, in this slot: from f0 on, every NW G-th one (f0 < 0: a frame before the launch)
+  const int gs = (int)blockIdx.z;
+  const int64_t b0 = a.F0 / NW, bf = b0 + (gs - b0 % a.G + a.G) % a.G;
+  if (bf * NW - a.F0 >= a.n_frames) return;  // (bf >= F0 / NW, so otherwise some wave has a frame)
+  int f0 = (int)(bf * NW - a.F0) + w;
+  const int fs = NW * a.G;
+  if (f0 < 0) f0 += fs;
   const int rows[2] = {u == 0 ? 0 : u, u == 0 ? N1 / 2 : N1 - u};
   uint32_t* X = reinterpret_cast<uint32_t*>(lds + w * WAVE_BYTES);
   float2* spec = reinterpret_cast<float2*>(lds + w * WAVE_BYTES + H * 16 * XS * 4);
@@ -358,8 +367,8 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   };
   // prefetches are unconditional (past the end a wave fetches its last frame again), so each frame waits
   // only for its own loads and the next frame's stay in flight
-  if (w < a.n_frames) fetch(w);
-  for (int f = w; f < a.n_frames; f += NW) {
+  if (f0 < a.n_frames) fetch(f0);
+  for (int f = f0; f < a.n_frames; f += fs) {
     uint32_t cur[2][H][4];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
@@ -367,7 +376,7 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
       for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) cur[r][h][jj] = raw[r][h][jj];
-    fetch(f + NW < a.n_frames ? f + NW : f);
+    fetch(f + fs < a.n_frames ? f + fs : f);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       f4v o[H][2];
@@ -442,7 +451,8 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   }
   __syncthreads();
   if (w == 0) {
-    double* acc = a.acc + (int64_t)(p * U + u) * 4 * N2;
+    double* acc = a.acc + gs * a.slot_stride + (int64_t)(p * U + u) * 4 * N2;
+    const bool first = a.F0 <= (int64_t)NW * gs;  // the slot holds no frame of this integration yet
 #pragma unroll
     for (int m = 0; m < SPL; ++m) {
       const int s = lane + 64 * m;
@@ -452,7 +462,7 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
 #pragma unroll
         for (int v = 0; v < NW - 1; ++v) t += part[((v * SPL + m) * 4 + k) * 64 + lane];
         t *= a.unscale;
-        acc[k * N2 + s] = a.first ? t : acc[k * N2 + s] + t;
+        acc[k * N2 + s] = first ? t : acc[k * N2 + s] + t;
       }
     }
   }
@@ -461,10 +471,16 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
 #define PS_LAUNCH(kernel, grid, block, l, ...) \
   hipExtLaunchKernelGGL(kernel, grid, block, 0, (l).stream, (l).start, (l).stop, 0, __VA_ARGS__)
 
-// int8 word paths (no window), or item-by-item decoding of any format with or without a window
+// int8 word paths, or item-by-item decoding of any format, with or without a window
 template <int R, int N2, int PREC, bool WIN>
-hipError_t colpass_mx_generic(int bits, const MxColArgs& a, const dim3& grid, const Launch& l) {
+hipError_t colpass_mx_mode(int bits, const MxColArgs& a, const dim3& grid, const Launch& l) {
   const dim3 block(256);
+  switch (a.mode) {
+    case 1: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 1, WIN>), grid, block, l, a); return hipGetLastError();
+    case 2: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 2, WIN>), grid, block, l, a); return hipGetLastError();
+    case 3: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 3, WIN>), grid, block, l, a); return hipGetLastError();
+    default: break;
+  }
   switch (bits) {
     case 2: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 2, 0, WIN>), grid, block, l, a); break;
     case 4: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 4, 0, WIN>), grid, block, l, a); break;
@@ -477,15 +493,9 @@ hipError_t colpass_mx_generic(int bits, const MxColArgs& a, const dim3& grid, co
 
 template <int R, int N2, int PREC>
 hipError_t colpass_mx_bits(int bits, const MxColArgs& a, int n_blocks, const Launch& l) {
-  const dim3 grid((unsigned)n_blocks), block(256);
-  if (a.col.win) return colpass_mx_generic<R, N2, PREC, true>(bits, a, grid, l);
-  switch (a.mode) {
-    case 1: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 1, false>), grid, block, l, a); break;
-    case 2: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 2, false>), grid, block, l, a); break;
-    case 3: PS_LAUNCH((k_colpass_mx<R, N2, PREC, 8, 3, false>), grid, block, l, a); break;
-    default: return colpass_mx_generic<R, N2, PREC, false>(bits, a, grid, l);
-  }
-  return hipGetLastError();
+  const dim3 grid((unsigned)n_blocks);
+  return a.col.win ? colpass_mx_mode<R, N2, PREC, true>(bits, a, grid, l)
+                   : colpass_mx_mode<R, N2, PREC, false>(bits, a, grid, l);
 }
 
 template <int PREC>
@@ -498,7 +508,7 @@ hipError_t colpass_mx_prec(int N1, int N2, int bits, const MxColArgs& a, int n_b
 
 template <int R>
 hipError_t rowpass_mx_r(int prec, int accum, const MxRowArgs& a, const Launch& l) {
-  const dim3 grid((unsigned)(a.N1 / 2), (unsigned)a.P), block(256);
+  const dim3 grid((unsigned)(a.N1 / 2), (unsigned)a.P, (unsigned)a.G), block(256);
   const bool kahan = accum == PS_ACC_KAHAN32;
   if (prec == PS_PREC_FP16) {
     if (kahan) PS_LAUNCH((k_rowpass_mx<R, PS_PREC_FP16, true>), grid, block, l, a);

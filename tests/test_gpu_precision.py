@@ -168,3 +168,38 @@ def test_precision_config_610_frames(env, config3, precision):
     e = np.max(np.abs(got - ref) / ref[:, 0:1, :], axis=2)
     say(f"  per-Stokes errors {e.tolist()}")
     assert np.all(e < 1e-3), e
+
+
+@pytest.mark.parametrize("log2n,streams,F,cuts", [(16, 2, 5, (0, 1, 5)), (16, 2, 37, (0, 3, 20, 37)), (17, 4, 19, (0, 6, 19)),
+                                                  (16, 4, 300, (0, 300)), (18, 2, 6, (0, 2, 6)), (18, 4, 3, (0, 3))])
+@pytest.mark.parametrize("window", ["rect", "hann"])
+def test_slots_and_windowed_words(env, log2n, streams, F, cuts, window):
+    """The 16-bit row pass's slots (blocks of four frames, fewer blocks than slots, launches that begin inside a block)
+    and the windowed word loads, each against item-by-item decoding and against one call: int8 streams in an order
+    that the word loader does not take (the pairs swapped) give the same rounding points.  Sums of products of at most
+    3e5 terms in FP64 or compensated FP32 and another order of the slots: 1e-6 of the mean power."""
+    torch, pk, dev = env
+    N = 1 << log2n
+    gen = torch.Generator(device=dev).manual_seed(log2n * 100 + F)
+    x = (torch.randn((F * N, streams), device=dev, generator=gen) * 16).round().clamp(-128, 127)
+    x[:, -1] = (0.5 * x[:, 0] + 0.5 * x[:, -1]).round()
+    packed = x.to(torch.int8).view(torch.uint8).reshape(-1)
+    pairs = ((0, 1),) if streams == 2 else ((0, 2), (1, 3))
+    # one stream more, never used: neither two nor four streams, so the codes are decoded item by item
+    wide = torch.cat([x, x[:, :1]], 1).to(torch.int8).view(torch.uint8).reshape(-1).contiguous()
+
+    def spectra(n_streams, data, steps):
+        plan = pk.Plan([pk.Instance(fft_len=N, bits=8, n_streams=n_streams, pairs=pairs, window=window, precision="fp16",
+                                    accum="kahan32")], device=dev)
+        plan.reset()
+        for lo, hi in zip(steps, steps[1:]):
+            plan.accumulate(data[lo * N * n_streams:hi * N * n_streams])
+        return plan.spectra()
+
+    say(f"N=2^{log2n} streams={streams} F={F} {window}")
+    got, nf = spectra(streams, packed, cuts)
+    one, _ = spectra(streams, packed, (0, F))
+    items, _ = spectra(streams + 1, wide, (0, F))
+    scale = got[:, :2].mean(dim=2).amax()
+    assert nf == F
+    assert float((got - one).abs().max() / scale) < 1e-6 and float((items - one).abs().max() / scale) < 1e-6

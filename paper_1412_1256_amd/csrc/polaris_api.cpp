@@ -377,6 +377,17 @@ int default_log2_n1(const ps_instance& c) {
   }
 }
 
+// The split of an FP32 instance whose schedule (may be null) leaves it open: as above, but 2^21 and 2^22 points run as
+// 512 x 4096 and 1024 x 4096 unless the schedule fixes a tile of the passes (tiles are those of the split above): columns
+// of 512 and 1024 points in blocks of whole or half cache lines, where 2048-point columns come in blocks of
+// four (2^24 samples of two int8 streams: 2^21 points 105 us against 126 as 1024 x 2048, 2^22 161 against 187 as
+// 2048 x 2048).
+int open_log2_n1(const ps_instance& c, const ps_schedule* s) {
+  const int m = ilog2_exact(c.fft_len);
+  if (m >= 21 && c.precision == PS_PREC_FP32 && !(s && (s->colpass_cols || s->rowpass_frames))) return m - 12;
+  return default_log2_n1(c);
+}
+
 int default_col_wgs(const ps_instance& c) {
   const int m = ilog2_exact(c.fft_len);
   if (c.precision != PS_PREC_FP32) return 1;
@@ -435,7 +446,7 @@ const char* schedule_error(const ps_instance& c, const ps_schedule& s, char* why
   static thread_local char buf[160];
   char* w = why ? why : buf;
   const int m = ilog2_exact(c.fft_len);
-  const int m1 = s.log2_n1 ? s.log2_n1 : default_log2_n1(c), m2 = m - m1;
+  const int m1 = s.log2_n1 ? s.log2_n1 : open_log2_n1(c, &s), m2 = m - m1;
   if (s.single_pass < 0 || s.single_pass > 2) {
     snprintf(w, 160, "single_pass %d not in 0..2", s.single_pass);
     return w;
@@ -467,7 +478,7 @@ const char* schedule_error(const ps_instance& c, const ps_schedule& s, char* why
     }
     return nullptr;
   }
-  if (m1 < 4 || m1 > 11 || m2 < 4 || m2 > 11) {
+  if (m1 < 4 || m1 > 11 || m2 < 4 || m2 > (s.log2_n1 ? 11 : 12)) {
     snprintf(w, 160, "split 2^%d x 2^%d outside 2^4 .. 2^11 per pass", m1, m2);
     return w;
   }
@@ -723,10 +734,6 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   // four streams as the pairs (0, 2) and (1, 3): one workgroup transforms both from the words it reads
   if (m.mode == 2 && c.n_pairs == 2 && c.pair_x[0] == 0 && c.pair_y[0] == 2 && c.pair_x[1] == 1 && c.pair_y[1] == 3)
     m.mode = 3;
-  // Windowed four-stream launches of 256-point columns: up to 2^24 points a pair the items' loads at use, with a
-  // workgroup per pair, were as fast or faster than the words of both pairs (2^17 points: 128 frames 99 against 105
-  // us, 20 frames 28.5 against 31.4; 300 frames 241 against 228).
-  if (m.mode == 3 && ca.win && I.N1 == 256 && (int64_t)ca.n_frames * I.N <= (int64_t(1) << 24)) m.mode = 0;
   if (ca.in_bytes == 0) m.mode = 0;  // the word paths address the launch's input with 32-bit offsets
   const int64_t per_frame = (int64_t)m.col.n_colblk * (m.mode == 3 ? 1 : ca.P);
   // two workgroups fit on a CU: two rounds of them, each looping over a group of frames, so that the second round
@@ -955,7 +962,7 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
     I.cfg = inst[i];
     I.N = inst[i].fft_len;
     I.m = ilog2_exact(I.N);
-    I.m1 = (sched && sched[i].log2_n1) ? sched[i].log2_n1 : default_log2_n1(I.cfg);
+    I.m1 = (sched && sched[i].log2_n1) ? sched[i].log2_n1 : open_log2_n1(I.cfg, sched ? &sched[i] : nullptr);
     I.m2 = I.m - I.m1;
     I.N1 = int64_t(1) << I.m1;
     I.N2 = int64_t(1) << I.m2;
@@ -968,9 +975,6 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
                                              : (I.fused ? default_slots_fused(I.cfg) : default_slots(I.cfg, (int)I.N1, (int)I.N2));
     I.fb = (sched && sched[i].rowpass_frames) ? sched[i].rowpass_frames
                                               : default_rowpass_frames(I.cfg, (int)I.N1, (int)I.N2, (int)I.G);
-    // a pass pair covers 2^25 points (a 256 MiB inter-pass buffer per pair, shared by the plan's instances),
-    // at least 64 frames, so its fixed cost (first loads, last stores, setup) is spread over many frames:
-    // 6-11 % faster than 2^24 points for 2^25-sample integrations of 2^13 .. 2^18-point frames
     I.chunk = inst[i].chunk_frames ? inst[i].chunk_frames : (int64_t)std::max<int64_t>(64, (int64_t(1) << 25) / I.N);
     // word loads of the column pass: 2-, 4- and 8-bit codes of two streams correlated as (0, 1), or of four
     // streams (any pairs)

@@ -533,6 +533,72 @@ __device__ __forceinline__ void wide_chain(float2 (&v)[16], int ts, const WideTw
   wide_pass<L, 2>(v, tw, ts, seq);
 }
 
+// ------------------------------------------------------------------------------------------------
+// transforms of N = 2^8 .. 2^12 points held as 16 points per thread (T = N / 16 threads): a first pass, a middle one
+// (radix 0: none) and a last pass of radix 16, whose outputs stay with the thread (thread ts ends with Z[ts + k T],
+// k < 16, where it also began with z[ts + k T])
+// ------------------------------------------------------------------------------------------------
+template <int N>
+struct Passes16 {
+  static constexpr int T = N / 16;                       // threads per frame
+  static constexpr int R0 = N == 256 || N == 4096 ? 16 : 8, R1 = N / 16 / R0 == 1 ? 0 : N / 16 / R0;
+  static constexpr bool WAVE = T <= 64;                  // a frame lives in one wave: no workgroup barriers
+  // LDS place of point e of a frame: one pad per R0 points.  The R0-strided writes of the first pass, the
+  // middle pass's writes and the unit-stride reads then fall on distinct banks (but for 2-way conflicts of the
+  // middle writes at N = 512), and every place is a per-thread base plus a constant.
+  static __host__ __device__ constexpr int at(int e) { return e + e / R0; }
+  static constexpr int LEN = N + N / R0;                 // points of a frame's buffer
+};
+
+template <int N>
+__device__ __forceinline__ void sync16() {
+  if constexpr (Passes16<N>::WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
+// Radix-R pass over the thread's 16 points: task i takes registers i + r 16/R, input r rotated by w[r - 1].
+template <int R, bool ROT, int NW>
+__device__ __forceinline__ void dft16(float2 (&v)[16], const float2 (&w)[NW]) {
+  constexpr int TASKS = 16 / R;
+#pragma unroll
+  for (int i = 0; i < TASKS; ++i) {
+    float2 t[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) t[r] = v[i + r * TASKS];
+    if constexpr (ROT) {
+#pragma unroll
+      for (int r = 1; r < R; ++r) t[r] = cmul(t[r], w[r - 1]);
+    }
+    Dft<R>::run(t);
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[i + r * TASKS] = t[r];
+  }
+}
+
+// The outputs of a pass (radix R, sub-transform length NS: output r of task j = ts + i T goes to point
+// (j / NS) NS R + j mod NS + r NS) through LDS to the next pass's inputs ts + k T.
+template <int N, int R, int NS>
+__device__ __forceinline__ void exchange16(float2 (&v)[16], const int ts, float2* __restrict__ seq) {
+  using F = Passes16<N>;
+  constexpr int TASKS = 16 / R, T = F::T;
+#pragma unroll
+  for (int i = 0; i < TASKS; ++i) {
+    const int j = ts + i * T, base = (j / NS) * NS * R + (j & (NS - 1));
+    // at(base + r NS): r NS and the run of base mod R0 (below NS or R0) never carry into each other
+    float2* q = seq + F::at(base);
+#pragma unroll
+    for (int r = 0; r < R; ++r) q[r * NS + r * NS / F::R0] = v[i + r * TASKS];
+  }
+  sync16<N>();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = seq[F::at(ts) + k * F::at(T)];
+}
+
 // FP64 complex arithmetic
 struct cd {
   double x, y;

@@ -13,69 +13,10 @@ namespace ps {
 
 namespace {
 
-// Radices of the passes: first, middle (0: none), and a last pass of radix 16, whose outputs stay with the thread
-// (thread ts ends with Z[ts + k T], k < 16, where it also began with z[ts + k T]).
+// threads of a workgroup, and frames (slots) side by side in it
 template <int N>
-struct FusedPasses {
-  static constexpr int T = N / 16;                       // threads per frame
-  static constexpr int R0 = N == 256 || N == 4096 ? 16 : 8, R1 = N / 16 / R0 == 1 ? 0 : N / 16 / R0;
-  static constexpr int NT = T < 64 ? 64 : T;             // threads of a workgroup
-  static constexpr int SPW = NT / T;                     // frames (slots) side by side in a workgroup
-  static constexpr bool WAVE = T <= 64;                  // a frame lives in one wave: no workgroup barriers
-  // LDS place of point e of a frame: one pad per R0 points.  The R0-strided writes of the first pass, the
-  // middle pass's writes and the unit-stride reads then fall on distinct banks (but for 2-way conflicts of the
-  // middle writes at N = 512), and every place is a per-thread base plus a constant.
-  static __host__ __device__ constexpr int at(int e) { return e + e / R0; }
-  static constexpr int LEN = N + N / R0;                 // points of a frame's buffer
-};
-
-template <int N>
-__device__ __forceinline__ void fused_sync() {
-  if constexpr (FusedPasses<N>::WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
-
-// Radix-R pass over the thread's 16 points: task i takes registers i + r 16/R, input r rotated by w[r - 1].
-template <int R, bool ROT, int NW>
-__device__ __forceinline__ void fused_dft(float2 (&v)[16], const float2 (&w)[NW]) {
-  constexpr int TASKS = 16 / R;
-#pragma unroll
-  for (int i = 0; i < TASKS; ++i) {
-    float2 t[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) t[r] = v[i + r * TASKS];
-    if constexpr (ROT) {
-#pragma unroll
-      for (int r = 1; r < R; ++r) t[r] = cmul(t[r], w[r - 1]);
-    }
-    Dft<R>::run(t);
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[i + r * TASKS] = t[r];
-  }
-}
-
-// The outputs of a pass (radix R, sub-transform length NS: output r of task j = ts + i T goes to point
-// (j / NS) NS R + j mod NS + r NS) through LDS to the next pass's inputs ts + k T.
-template <int N, int R, int NS>
-__device__ __forceinline__ void fused_exchange(float2 (&v)[16], const int ts, float2* __restrict__ seq) {
-  using F = FusedPasses<N>;
-  constexpr int TASKS = 16 / R, T = F::T;
-#pragma unroll
-  for (int i = 0; i < TASKS; ++i) {
-    const int j = ts + i * T, base = (j / NS) * NS * R + (j & (NS - 1));
-    // at(base + r NS): r NS and the run of base mod R0 (below NS or R0) never carry into each other
-    float2* q = seq + F::at(base);
-#pragma unroll
-    for (int r = 0; r < R; ++r) q[r * NS + r * NS / F::R0] = v[i + r * TASKS];
-  }
-  fused_sync<N>();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = seq[F::at(ts) + k * F::at(T)];
+constexpr int fused_nt() {
+  return N / 16 < 64 ? 64 : N / 16;
 }
 
 // Raw words of a thread's 16 time samples of a frame.  MODE 1 (two streams, the pair (0, 1)) and 2 (four streams):
@@ -83,7 +24,7 @@ __device__ __forceinline__ void fused_exchange(float2 (&v)[16], const int ts, fl
 // float) of each stream's item.
 template <int N, int BITS, int MODE>
 struct FusedLoader {
-  static constexpr int T = FusedPasses<N>::T;
+  static constexpr int T = Passes16<N>::T;
   static constexpr int TB = MODE == 1 ? 2 * BITS : 4 * BITS;  // bits of a time sample's word
   uint32_t x[16], y[MODE == 0 ? 16 : 1];
   template <class P>
@@ -139,9 +80,9 @@ struct FusedLoader {
 // two barriers per pass.  N / 16 threads per frame leave room for the twiddles, the window and the eight channels'
 // sums in registers (240); every pass of radix 16 saves an exchange against three of radix 8.
 template <int N, int BITS, int MODE>
-__global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
-  using F = FusedPasses<N>;
-  constexpr int T = F::T, SPW = F::SPW, R0 = F::R0, R1 = F::R1;
+__global__ void __launch_bounds__(fused_nt<N>()) k_fused(FusedArgs a) {
+  using F = Passes16<N>;
+  constexpr int T = F::T, SPW = fused_nt<N>() / T, R0 = F::R0, R1 = F::R1;
   // frames of several waves: two buffers, so that three barriers per frame suffice (see the frame loop)
   constexpr int NBUF = F::WAVE ? 1 : 2;
   __shared__ __align__(16) float2 buf[SPW][NBUF][F::LEN];
@@ -208,19 +149,19 @@ __global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
     ld.fetch(frame_base(j + 1 < n_run ? j + 1 : j), ts, a.S, sx, sy);
     // Buffers of frames of several waves: the first exchange uses b0, the second b1 and the mirror b0 again, and the
     // next frame the other way round, so that a buffer's readers have always passed a barrier before it is written.
-    fused_dft<R0, false>(v, w2);
-    fused_exchange<N, R0, 1>(v, ts, b0);
+    dft16<R0, false>(v, w2);
+    exchange16<N, R0, 1>(v, ts, b0);
     if constexpr (R1 != 0) {
-      if constexpr (F::WAVE) fused_sync<N>();
-      fused_dft<R1, true>(v, w1);
-      fused_exchange<N, R1, R0>(v, ts, b1);
+      if constexpr (F::WAVE) sync16<N>();
+      dft16<R1, true>(v, w1);
+      exchange16<N, R1, R0>(v, ts, b1);
     }
-    fused_dft<16, true>(v, w2);
+    dft16<16, true>(v, w2);
     // Mirror: Z[N - k] of channel k = ts + r T is register 15 - r of thread T - ts (of thread 0: its own 16 - r).
-    if constexpr (F::WAVE) fused_sync<N>();
+    if constexpr (F::WAVE) sync16<N>();
 #pragma unroll
     for (int i = 0; i < 8; ++i) b0[i * T + ts] = v[8 + i];
-    fused_sync<N>();
+    sync16<N>();
     if (SPW == 1 || j < n_loc) {
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
@@ -236,7 +177,7 @@ __global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
         sum[3][r] += (double)(sx_ * dx_ + sy_ * dy_);
       }
     }
-    if constexpr (F::WAVE) fused_sync<N>();
+    if constexpr (F::WAVE) sync16<N>();
   }
   // The slot in its layout, two products at a time through LDS (one pad per N1 channels), so that the stores of a
   // row are consecutive: the threads' channels alone lie N2 * 4 doubles apart.
@@ -244,7 +185,7 @@ __global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
   double* const d = reinterpret_cast<double*>(buf[sub][0]);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if constexpr (F::WAVE) fused_sync<N>();
+    if constexpr (F::WAVE) sync16<N>();
     else __syncthreads();
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -252,7 +193,7 @@ __global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
       d[k + (k >> sh)] = sum[2 * h][r];
       d[half_len + k + (k >> sh)] = sum[2 * h + 1][r];
     }
-    fused_sync<N>();
+    sync16<N>();
     if (n_loc) {
 #pragma unroll
       for (int r = 0; r < 8; ++r) {
@@ -269,8 +210,8 @@ __global__ void __launch_bounds__(FusedPasses<N>::NT) k_fused(FusedArgs a) {
 
 template <int N, int BITS>
 void fused_mode(int mode, const FusedArgs& a, const Launch& l) {
-  using F = FusedPasses<N>;
-  const dim3 grid((unsigned)((a.G + F::SPW - 1) / F::SPW), (unsigned)a.P), block(F::NT);
+  constexpr int NT = fused_nt<N>(), SPW = 16 * NT / N;
+  const dim3 grid((unsigned)((a.G + SPW - 1) / SPW), (unsigned)a.P), block(NT);
   if constexpr (BITS <= 8) {
     if (mode == 1) {
       hipExtLaunchKernelGGL((k_fused<N, BITS, 1>), grid, block, 0, l.stream, l.start, l.stop, 0, a);

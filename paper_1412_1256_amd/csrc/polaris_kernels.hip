@@ -519,6 +519,122 @@ __global__ void __launch_bounds__((rowpass_threads<L, UB, FB, SQ>()))
 }
 
 // ------------------------------------------------------------------------------------------------
+// row pass of rows held as 16 points per thread (L = 4096): a workgroup owns one unit, L / 16 threads per row, and walks
+// its slot's frames one by one, the next frame's row on its way while the current one is transformed.  Each thread
+// ends with the bins ts + r T of its row, owns the channel slots of r < 8 for the whole launch, and finds their
+// partner bins among the upper halves that the partner row's threads put into LDS (8 exchanges, where staging both
+// spectra takes 16 writes and 16 reads).
+// Bound by the latency of its three barriers per frame at two waves per SIMD (3.1 TB/s) and, over few frames, by
+// the accumulators' and the scattered Stokes stores: 8 frames of 2^21 points 68 us with the Stokes.
+// ------------------------------------------------------------------------------------------------
+template <int L, bool STOKES = false>
+__device__ __forceinline__ void row16_tile(const RowArgs& a, const int u, const int p, const int g,
+                                           const OutArgs* o = nullptr) {
+  using F = Passes16<L>;
+  constexpr int T = F::T, R0 = F::R0, R1 = F::R1;
+  static_assert(!F::WAVE && R1 != 0, "rows of several waves, three passes");
+  __shared__ __align__(16) float2 buf[2][2][F::LEN];  // [buffer][row]
+  const int rr = (int)threadIdx.x / T, ts = (int)threadIdx.x % T;
+  const int U = a.N1 / 2;
+  const int row = (u == 0) ? (rr ? U : 0) : (rr ? a.N1 - u : u);
+  // this slot's frames of the launch: f = f_first + j G, j < n_loc
+  const int f_first = (int)(((int64_t)g - a.F0 % a.G + a.G) % a.G);
+  const int n_loc = f_first < a.n_frames ? (a.n_frames - f_first + a.G - 1) / a.G : 0;
+  if (n_loc == 0) return;
+  const bool prior = a.F0 > g;  // the slot already holds frames of this integration
+
+  float2 w1[R1 - 1], w2[15];
+#pragma unroll
+  for (int r = 1; r < R1; ++r) w1[r - 1] = a.tw_row[r * (ts & (R0 - 1)) * (L / (R0 * R1))];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) w2[r - 1] = a.tw_row[r * ts];
+  // channel slots: bins ts + r T, r < 8, of this row
+  double* const acc = a.acc + (int64_t)g * a.slot_stride + ((int64_t)(p * U + u) * 4) * L + rr * (L / 2) + ts;
+  double sum[4][8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[q][r] = prior ? acc[q * L + r * T] : 0.0;
+
+  // bin (row, k2) pairs with bin N - k: the other row's L - 1 - k2, in unit 0 the same row's (row 0: L - k2)
+  const bool dc = u == 0 && rr == 0;
+  const int prow = u == 0 ? rr : 1 - rr, pts = dc ? (ts ? T - ts : 0) : T - 1 - ts;
+  const int64_t fstride = (int64_t)a.P * a.N1 * L * a.G;
+  const float2* src = a.T + (((int64_t)f_first * a.P + p) * a.N1 + row) * (int64_t)L + ts;
+  float2 nx[16];
+  auto fetch = [&](int j) {
+    const float2* q = src + (int64_t)j * fstride;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) nx[k] = q[k * T];
+  };
+  fetch(0);
+  for (int j = 0; j < n_loc; ++j) {
+    float2 v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = nx[k];
+    fetch(j + 1 < n_loc ? j + 1 : j);  // (unconditional: the last frame reads itself again)
+    // The first exchange uses b0, the second b1 and the mirror b0 again, and the next frame the other way round, so
+    // that a buffer's readers have always passed a barrier before it is written.
+    float2(*const b0)[F::LEN] = buf[j & 1];
+    float2(*const b1)[F::LEN] = buf[1 - (j & 1)];
+    dft16<R0, false>(v, w2);
+    exchange16<L, R0, 1>(v, ts, b0[rr]);
+    dft16<R1, true>(v, w1);
+    exchange16<L, R1, R0>(v, ts, b1[rr]);
+    dft16<16, true>(v, w2);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b0[rr][i * T + ts] = v[8 + i];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float2 m = b0[prow][(7 - r) * T + pts], own = r ? v[16 - r] : v[0];
+      const float2 A = v[r], B = dc && ts == 0 ? own : m;
+      const float sx_ = A.x + B.x, sy_ = A.y - B.y;   // A + conj(B) = 2 X
+      const float dx_ = A.x - B.x, dy_ = A.y + B.y;   // A - conj(B) = 2i Y
+      sum[0][r] += (double)(sx_ * sx_ + sy_ * sy_);
+      sum[1][r] += (double)(dx_ * dx_ + dy_ * dy_);
+      sum[2][r] += (double)(sx_ * dy_ - sy_ * dx_);   // Re of i (s conj d)
+      sum[3][r] += (double)(sx_ * dx_ + sy_ * dy_);   // Im of i (s conj d)
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q * L + r * T] = sum[q][r];
+  if constexpr (STOKES) {
+    const double scale = o->sumw2_dev ? 1.0 / (o->n_frames * o->sumw2_dev[0]) : o->scale;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      stokes_write(*o, p, (int64_t)(ts + r * T) * a.N1 + row, scale, 0.25 * sum[0][r], 0.25 * sum[1][r],
+                   0.25 * sum[2][r], 0.25 * sum[3][r]);
+  }
+}
+
+template <int L>
+__global__ void __launch_bounds__(L / 8) k_row16(RowArgs a) {
+  row16_tile<L>(a, (int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z);
+}
+
+// with the Stokes spectra (one slot), units renumbered as in k_rowpass_stokes
+template <int L>
+__global__ void __launch_bounds__(L / 8) k_row16_stokes(RowArgs a, OutArgs o) {
+  const int nbx = (int)gridDim.x;
+  const int lin = xcd_remap((int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
+  row16_tile<L, true>(a, lin % nbx, lin / nbx, 0, &o);
+}
+
+template <int L>
+__global__ void __launch_bounds__(L / 8)
+    k_row16_batch(const RowArgs* __restrict__ tasks, const int32_t* __restrict__ tile_end, int n_tasks) {
+  const int tile = (int)blockIdx.x;
+  const int t = batch_task(tile_end, n_tasks, tile);
+  const int local = tile - (t ? tile_end[t - 1] : 0);
+  const RowArgs a = load_const(tasks + t);
+  const int nbx = a.N1 / 2;
+  row16_tile<L>(a, local % nbx, (local / nbx) % a.P, local / (nbx * a.P));
+}
+
+// ------------------------------------------------------------------------------------------------
 // output: accumulators -> natural channel order (raw spectra, or calibrated Stokes by Eq. 2)
 // ------------------------------------------------------------------------------------------------
 
@@ -784,10 +900,22 @@ static hipError_t rowpass_launch(const RowArgs& a, const Launch& s, const OutArg
   return hipGetLastError();
 }
 
+template <int L>
+static hipError_t row16_launch(const RowArgs& a, const Launch& s, const OutArgs* o) {
+  const dim3 grid((unsigned)(a.N1 / 2), (unsigned)a.P, (unsigned)a.G), block(L / 8);
+  if (o) {
+    if (a.G != 1) return hipErrorInvalidValue;
+    PS_LAUNCH(k_row16_stokes<L>, grid, block, s, a, *o);
+  } else {
+    PS_LAUNCH(k_row16<L>, grid, block, s, a);
+  }
+  return hipGetLastError();
+}
+
 // frames per row-pass workgroup batch: the default of each N2, and 4 for N2 = 256 and 512
-int rowpass_frames(int N2) { return N2 >= 2048 ? 2 : (N2 >= 1024 ? 4 : 8); }
+int rowpass_frames(int N2) { return N2 >= 4096 ? 1 : (N2 >= 2048 ? 2 : (N2 >= 1024 ? 4 : 8)); }
 bool rowpass_has(int N2, int fb) {
-  if (fb == rowpass_frames(N2)) return N2 >= 16 && N2 <= 2048;
+  if (fb == rowpass_frames(N2)) return N2 >= 16 && N2 <= 4096;
   return (N2 == 256 || N2 == 512) && fb == 4;
 }
 
@@ -807,6 +935,7 @@ hipError_t launch_rowpass(int N2, int fb, const RowArgs& a, const Launch& s, con
     case 512: return rowpass_launch<512, 1, 8, SQ>(a, s, o);
     case 1024: return rowpass_launch<1024, 1, 4, 1>(a, s, o);
     case 2048: return rowpass_launch<2048, 1, 2, 1>(a, s, o);
+    case 4096: return row16_launch<4096>(a, s, o);
     default: return hipErrorInvalidValue;
   }
 }
@@ -885,6 +1014,9 @@ hipError_t launch_rowpass_batch(int N2, int fb, const BatchArgs& b, const Launch
     case 512: return rowpass_batch_launch<512, 1, 8, SQ>(b, s);
     case 1024: return rowpass_batch_launch<1024, 1, 4, 1>(b, s);
     case 2048: return rowpass_batch_launch<2048, 1, 2, 1>(b, s);
+    case 4096:
+      PS_LAUNCH_BATCH(k_row16_batch<4096>, 512, b.total, s, static_cast<const RowArgs*>(b.tasks), b.tile_end, b.n_tasks);
+      return hipGetLastError();
     default: return hipErrorInvalidValue;
   }
 }

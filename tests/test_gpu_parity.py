@@ -414,3 +414,39 @@ def test_table1_modes(pk, torch_dev, mode, F):
     e = stokes_err(st, ref)
     say(f"  spectra err {e_spec.max()} stokes err {e.tolist()}")
     assert np.all(e_spec < TOL) and np.all(e < TOL), (e_spec, e)
+
+
+@pytest.mark.parametrize("log2n,bits,streams", [(21, 8, 2), (21, 2, 4), (22, 4, 2), (22, 8, 2)])
+def test_rows_of_4096_points(log2n, bits, streams):
+    """2^21 and 2^22 points as 512 and 1024 columns of rows held 16 points per thread: every unit (row 0 with N1/2, whose
+    bins pair within themselves, and the mirrored rows), a sum continued by a second call, both pairs of four streams,
+    the Stokes epilogue and the grouped launch.  Against the oracle normwise 1e-5; split calls, the grouped plan and the
+    epilogue bitwise equal."""
+    torch = pytest.importorskip("torch")
+    import paper_1412_1256_amd as pk
+    dev = torch.device("cuda:0")
+    N, F = 1 << log2n, 3
+    rng = np.random.default_rng(log2n * 10 + bits)
+    packed_np = rng.integers(0, 256, N * F * streams * bits // 8, dtype=np.uint8)
+    pairs = [(0, 1)] if streams == 2 else [(0, 2), (1, 3)]
+    inst = synth.gen._instance(packed_np, bits, streams, N, F, window="hann", pairs=pairs)
+    acc, _, _, _ = oracle.run_instance(inst)
+    packed = torch.from_numpy(packed_np).to(dev)
+    cut = N * streams * bits // 8
+
+    def spectra(cuts=(0, F), n_inst=1):
+        plan = pk.Plan([pk.Instance.from_synth(inst)] * n_inst, device=dev)
+        plan.reset()
+        for lo, hi in zip(cuts, cuts[1:]):
+            plan.accumulate([packed[lo * cut:hi * cut]] * n_inst)
+        st = plan.stokes(inst=n_inst - 1)
+        return plan.spectra(inst=n_inst - 1)[0].cpu().numpy(), st
+
+    print(f"rows of 4096: N=2^{log2n} bits={bits} streams={streams}", flush=True)
+    one, st = spectra()
+    scale = np.mean(acc[:, 0:1, :], axis=2, keepdims=True)
+    assert np.max(np.abs(one - acc) / scale) < 1e-5
+    assert np.array_equal(spectra(cuts=(0, 1, F))[0], one) and np.array_equal(spectra(n_inst=2)[0], one)
+    plan = pk.Plan([pk.Instance.from_synth(inst)], device=dev)
+    plan.reset()
+    assert torch.equal(plan.accumulate_stokes(packed)[0], st)

@@ -395,6 +395,20 @@ int default_col_wgs(const ps_instance& c) {
   return (m >= 14 && m <= 16) ? 2 : 1;
 }
 
+// Frames of a pass pair: its fixed cost (first loads, last stores, set-up) is spread over many frames, while the
+// buffer between the passes should fit the last-level cache (256 MiB).  FP32 passes: 2^25 points of all pairs (a
+// 256 MiB buffer), at least 64 frames: 6-11 % faster than 2^24 points at 2^13 .. 2^18; two pairs of 2^25 points each
+// are 10-14 % slower than of 2^24 (2^18 x 256 frames, 4-bit: 597 against 515 us; 2^16 x 1024: 540 and 481).  The window
+// adjoint takes the passes' buffer over when it holds the whole integration, so a learnable window keeps 2^25 points
+// a pair.  16-bit passes, whose workgroups sum and store per launch, gain more from long launches: 2^26 points a
+// pair in the same bytes (2^18 x 610 frames, two pairs: 839 us against 895 with 2^25; one pair: 512 and 558).
+int64_t default_chunk(const ps_instance& c) {
+  int64_t points = int64_t(1) << 25;
+  if (c.precision != PS_PREC_FP32) points *= 2;
+  else if (c.window != PS_WIN_TAPS) points /= c.n_pairs;
+  return std::max<int64_t>(64, points / c.fft_len);
+}
+
 // the single pass runs FP32 transforms of 2^8 .. 2^12 points
 bool fused_eligible(const ps_instance& c) {
   const int m = ilog2_exact(c.fft_len);
@@ -975,7 +989,7 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
                                              : (I.fused ? default_slots_fused(I.cfg) : default_slots(I.cfg, (int)I.N1, (int)I.N2));
     I.fb = (sched && sched[i].rowpass_frames) ? sched[i].rowpass_frames
                                               : default_rowpass_frames(I.cfg, (int)I.N1, (int)I.N2, (int)I.G);
-    I.chunk = inst[i].chunk_frames ? inst[i].chunk_frames : (int64_t)std::max<int64_t>(64, (int64_t(1) << 25) / I.N);
+    I.chunk = inst[i].chunk_frames ? inst[i].chunk_frames : default_chunk(I.cfg);
     // word loads of the column pass: 2-, 4- and 8-bit codes of two streams correlated as (0, 1), or of four
     // streams (any pairs)
     if (inst[i].bits <= 8 && inst[i].n_streams == 2 && inst[i].n_pairs == 1 && inst[i].pair_x[0] == 0 &&
@@ -999,7 +1013,7 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
     I.off_hist = off; off = align_up(off + (size_t)I.cfg.n_pairs * 2 * (size_t)I.hist_bins() * 8);
     I.off_tw_full = off; off = align_up(off + I.tw_full.size() * 4);
     I.off_stage = off; off = align_up(off + 2 * I.tail_bytes());
-    t_pool = std::max(t_pool, (size_t)I.chunk * (size_t)I.cfg.n_pairs * (size_t)I.N * 8);
+    t_pool = std::max(t_pool, (size_t)I.chunk * (size_t)I.cfg.n_pairs * (size_t)I.N * (I.mx() ? 4 : 8));
     I.off_acc = off; off = align_up(off + I.acc_bytes());
     if (I.G > ps::kDirectSlots) {
       I.off_sumacc = off; off = align_up(off + I.slot_doubles() * 8);

@@ -396,28 +396,31 @@ class Plan:
                            psi: float = 0.0, want=("gain_x", "gain_y", "dterms", "taps")):
         I = self.instances[inst]
         torch = self.torch
-        gain_x, gain_y, dterms = (self._as_f32(gain_x), self._as_f32(gain_y), self._as_f32(dterms))
         P, Cn = I.n_pairs, I.channels
+        empty = lambda *shape: torch.empty(shape, dtype=torch.float32, device=self.device)
         outs = {}
-        grad = _CalGrad()
         if "gain_x" in want:
-            outs["gain_x"] = torch.empty((P, Cn, 2), dtype=torch.float32, device=self.device)
-            grad.d_gain_x = outs["gain_x"].data_ptr()
+            outs["gain_x"] = empty(P, Cn, 2)
         if "gain_y" in want:
-            outs["gain_y"] = torch.empty((P, Cn, 2), dtype=torch.float32, device=self.device)
-            grad.d_gain_y = outs["gain_y"].data_ptr()
+            outs["gain_y"] = empty(P, Cn, 2)
         if "dterms" in want:
-            outs["dterms"] = torch.empty((P, 4), dtype=torch.float32, device=self.device)
-            grad.d_dterms = outs["dterms"].data_ptr()
+            outs["dterms"] = empty(P, 4)
         if "taps" in want and I.window == "taps":
-            outs["taps"] = torch.empty((I.n_taps,), dtype=torch.float32, device=self.device)
-            grad.d_taps = outs["taps"].data_ptr()
+            outs["taps"] = empty(I.n_taps)
+        self._backward_into(outs, packed, dL_diquv, inst, gain_x, gain_y, dterms, psi)
+        return outs
+
+    def _backward_into(self, outs, packed, dL_diquv, inst, gain_x, gain_y, dterms, psi):
+        """calibrate_backward into given tensors: outs maps gradient names to contiguous float32 or complex64 tensors."""
+        I = self.instances[inst]
+        gain_x, gain_y, dterms = (self._as_f32(gain_x), self._as_f32(gain_y), self._as_f32(dterms))
+        grad = _CalGrad(*[None if outs.get(k) is None else outs[k].data_ptr()
+                          for k in ("gain_x", "gain_y", "dterms", "taps")])
         cal = self._cal(gain_x, gain_y, dterms, psi)
         n_samples = packed.numel() * 8 // (I.n_streams * I.bits)
-        g = dL_diquv.to(torch.float32).contiguous()
+        g = dL_diquv.to(self.torch.float32).contiguous()
         _check(lib().ps_calibrate_backward(self._h, inst, _ptr(packed), n_samples, C.byref(cal), _ptr(g),
                                            C.byref(grad)))
-        return outs
 
     def integration_id(self, inst: int = 0) -> int:
         """Changes whenever the integration a gradient would be taken of changes (see ps_integration_id)."""
@@ -464,6 +467,10 @@ class Plan:
         if t is None:
             return None
         torch = self.torch
+        # the usual case, float32 or complex64 data in place (the same bytes): nothing to convert
+        if t.dtype in (torch.complex64, torch.float32) and t.device == self.workspace.device and t.is_contiguous():
+            if not (t.is_conj() or t.is_neg()):
+                return t
         if t.is_complex():
             t = torch.view_as_real(t.to(torch.complex64))
         return t.to(device=self.device, dtype=torch.float32).contiguous()

@@ -18,10 +18,9 @@ class StokesFn(torch.autograd.Function):
         if taps is not None:
             plan.set_window_taps(taps.detach())
         plan.reset()
-        plan.accumulate(packed)
-        iquv = plan.stokes(gain_x=None if gain_x is None else gain_x.detach(),
-                           gain_y=None if gain_y is None else gain_y.detach(),
-                           dterms=None if dterms is None else dterms.detach(), psi=psi)
+        iquv = plan.accumulate_stokes(packed, gain_x=None if gain_x is None else gain_x.detach(),
+                                      gain_y=None if gain_y is None else gain_y.detach(),
+                                      dterms=None if dterms is None else dterms.detach(), psi=psi)[0]
         ctx.save_for_backward(*(t if t is not None else torch.empty(0) for t in (gain_x, gain_y, dterms, taps)))
         ctx.present = tuple(t is not None for t in (gain_x, gain_y, dterms, taps))
         ctx.plan, ctx.packed, ctx.psi = plan, packed, psi
@@ -36,21 +35,20 @@ class StokesFn(torch.autograd.Function):
             raise PolarisError(4, "the plan's integration changed after this forward; run the backward before "
                                   "the next forward on the same plan, or use one plan per forward")
         gx, gy, dt, taps = (t if p else None for t, p in zip(ctx.saved_tensors, ctx.present))
-        want = []
+        plan = ctx.plan
+        inst = plan.instances[0]
+        d_gx = d_gy = d_dt = d_taps = None
+        # complex gradients are written as the (re, im) pairs that complex64 tensors hold
         if ctx.needs_input_grad[0]:
-            want.append("gain_x")
+            d_gx = torch.empty((inst.n_pairs, inst.channels), dtype=torch.complex64, device=plan.device)
         if ctx.needs_input_grad[1]:
-            want.append("gain_y")
+            d_gy = torch.empty((inst.n_pairs, inst.channels), dtype=torch.complex64, device=plan.device)
         if ctx.needs_input_grad[2]:
-            want.append("dterms")
-        if ctx.needs_input_grad[3]:
-            want.append("taps")
-        out = ctx.plan.calibrate_backward(ctx.packed, g_iquv.contiguous(), gain_x=gx, gain_y=gy, dterms=dt,
-                                          psi=ctx.psi, want=tuple(want))
-        d_gx = torch.view_as_complex(out["gain_x"]) if "gain_x" in out else None
-        d_gy = torch.view_as_complex(out["gain_y"]) if "gain_y" in out else None
-        d_dt = torch.view_as_complex(out["dterms"].view(-1, 2, 2)) if "dterms" in out else None
-        d_taps = out.get("taps")
+            d_dt = torch.empty((inst.n_pairs, 2), dtype=torch.complex64, device=plan.device)
+        if ctx.needs_input_grad[3] and inst.window == "taps":
+            d_taps = torch.empty((inst.n_taps,), dtype=torch.float32, device=plan.device)
+        plan._backward_into(dict(gain_x=d_gx, gain_y=d_gy, dterms=d_dt, taps=d_taps), ctx.packed, g_iquv, 0, gx, gy, dt,
+                            ctx.psi)
         return d_gx, d_gy, d_dt, d_taps, None, None, None
 
 

@@ -736,7 +736,7 @@ __global__ void __launch_bounds__(kColsSeries * kColsSlices) k_allan_cols(AllanA
 // untested; a round of lags with a non-finite sum in the workgroup is taken again with each term tested.  A fixed
 // order: runs of a phase in turn, phases of a wave by butterfly, waves in order.
 // Bound by vector issue (per term a conversion, three FP64 operations and an address): 1800 integrations of 131072
-// channels at 8 lags in 630 us, 290 us of it the read alone (3.3 TB/s in 32-byte rows); 890 us by the window form
+// channels at 8 lags in 619 us, 290 us of it the read alone (3.3 TB/s in 32-byte rows); 890 us by the window form
 // below, which reads and converts both outer samples of every term, with two barriers per 64 points.
 template <int S, bool TEST, bool CUT>
 __device__ __forceinline__ void series_lag(const float* __restrict__ w, const int P, const int L, const int m,
@@ -791,8 +791,10 @@ __device__ __forceinline__ void series_lag(const float* __restrict__ w, const in
     if (k & 4) terms(std::integral_constant<int, 4>{});
     if (k & 2) terms(std::integral_constant<int, 2>{});
     if (k & 1) terms(std::integral_constant<int, 1>{});
-    const double d = (double)w[more ? at : s] - 2.0 * x1 + x0;
-    if (TEST ? more : true) add(more ? d : 0.0);
+    if (CUT || i0 < rem) {  // (the same for every lane)
+      const double d = (double)w[more ? at : s] - 2.0 * x1 + x0;
+      if (TEST ? more : true) add(more ? d : 0.0);
+    }
     const bool own = i0 + ph < items;
     sum += own ? part : 0.0;
     if constexpr (TEST) cnt += own ? n : 0.0;

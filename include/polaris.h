@@ -282,7 +282,9 @@ ps_status ps_integration_id(ps_plan_t plan, int32_t inst, uint64_t* id);
 
 /* Integration state for checkpoint and resume: the accumulators and, for overlapped segmentation, the
  * samples waiting for the next call (the frame count is passed separately).  Device buffers of
- * ps_state_bytes bytes; export and import are enqueued on the plan's stream. */
+ * ps_state_bytes bytes; export and import are enqueued on the plan's stream.  The accumulators are kept in the
+ * layout of the instance's schedule (split, slots): a state belongs to plans of the same fields, schedule and
+ * build of this library, since another build's defaults may differ. */
 ps_status ps_state_bytes(ps_plan_t plan, int32_t inst, size_t* bytes);
 ps_status ps_state_export(ps_plan_t plan, int32_t inst, void* dst_dev, int64_t* n_frames);
 ps_status ps_state_import(ps_plan_t plan, int32_t inst, const void* src_dev, int64_t n_frames);

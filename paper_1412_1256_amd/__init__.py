@@ -448,6 +448,9 @@ class Plan:
         return buf, nf.value
 
     def state_import(self, buf, n_frames: int, inst: int = 0):
+        need = self.state_bytes(inst)
+        if buf is not None and buf.numel() * buf.element_size() < need:  # another schedule's state (or build's)
+            raise ValueError(f"instance {inst} has a state of {need} bytes, got {buf.numel() * buf.element_size()}")
         _check(lib().ps_state_import(self._h, inst, _ptr(buf), int(n_frames)))
 
     KERNELS = ("colpass", "rowpass", "stokes", "spectra", "backward", "other")

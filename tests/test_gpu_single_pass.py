@@ -254,3 +254,17 @@ def test_word_loads_slots_and_parts(env, log2n, bits, streams):
         plan.accumulate(raw[1:])
         off, _ = plan.spectra()
         assert np.array_equal(off.cpu().numpy(), spec)
+
+
+@pytest.mark.parametrize("slots", [64, 512])
+def test_state_of_fewer_slots_refused(env, slots):
+    """A state has its plan's slots: one of half as many is refused before it is read."""
+    torch, pk, dev = env
+    inst = pk.Instance(fft_len=1 << 10, bits=2)
+    plan = pk.Plan([inst], device=dev, schedules=[pk.Schedule(rowpass_slots=slots, single_pass=1)])
+    less = pk.Plan([inst], device=dev, schedules=[pk.Schedule(rowpass_slots=slots // 2, single_pass=1)])
+    less.accumulate(torch.zeros(2 * (1 << 10) * 4 // 8, dtype=torch.uint8, device=dev))
+    state, n = less.state_export()
+    with pytest.raises(ValueError):
+        plan.state_import(state, n)
+    less.state_import(state, n)

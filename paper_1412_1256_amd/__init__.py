@@ -431,8 +431,9 @@ class Plan:
     def set_window_taps(self, taps, inst: int = 0):
         t = self._as_f32(taps)
         n = self.instances[inst].n_taps
-        if n > 0 and t.numel() != n:  # (an instance without a taps window is refused by the library)
-            raise ValueError(f"instance {inst} has {n} window taps, got {t.numel()}")
+        floats = t.numel() * (2 if t.is_complex() else 1)  # (a complex64 tensor stands for its (re, im) pairs)
+        if n > 0 and floats != n:  # (an instance without a taps window is refused by the library)
+            raise ValueError(f"instance {inst} has {n} window taps, got {floats}")
         _check(lib().ps_set_window_taps(self._h, inst, _ptr(t)))
         self._taps_keepalive = t
 
@@ -467,6 +468,8 @@ class Plan:
         return {k: (ms[i], n[i]) for i, k in enumerate(self.KERNELS) if n[i]}
 
     def _as_f32(self, t):
+        """A tensor whose memory holds t as contiguous float32 on the plan's device: a float32 tensor, or a complex64 one,
+        whose elements count as two floats each."""
         if t is None:
             return None
         torch = self.torch

@@ -18,9 +18,11 @@ class StokesFn(torch.autograd.Function):
         if taps is not None:
             plan.set_window_taps(taps.detach())
         plan.reset()
-        iquv = plan.accumulate_stokes(packed, gain_x=None if gain_x is None else gain_x.detach(),
-                                      gain_y=None if gain_y is None else gain_y.detach(),
-                                      dterms=None if dterms is None else dterms.detach(), psi=psi)[0]
+        # the calibration and the output are instance 0's; a plan's other instances only accumulate
+        inst, others = plan.instances[0], [None] * (len(plan.instances) - 1)
+        cal = tuple(None if t is None else t.detach() for t in (gain_x, gain_y, dterms)) + (psi,)
+        iquv = torch.empty((inst.n_pairs, 4, inst.channels), dtype=torch.float32, device=plan.device)
+        plan.accumulate_stokes(packed, outs=[iquv] + others, cals=[cal] + others)
         ctx.save_for_backward(*(t if t is not None else torch.empty(0) for t in (gain_x, gain_y, dterms, taps)))
         ctx.present = tuple(t is not None for t in (gain_x, gain_y, dterms, taps))
         ctx.plan, ctx.packed, ctx.psi = plan, packed, psi

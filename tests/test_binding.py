@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_1412_1256_amd as pk
+from paper_1412_1256_amd import autograd
 
 
 class Recorder:
@@ -59,3 +60,24 @@ def test_window_taps_count_floats(recorder, dtype, count, ok):
     got = list((C.c_float * 64).from_address(ptr.value))
     want = torch.view_as_real(taps).reshape(-1) if taps.is_complex() else taps
     assert got == want.to(torch.float32).tolist()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_differentiable_stokes_calibrates_instance_0(recorder, n):
+    """The differentiable Stokes of a plan are instance 0's: its calibration and output go to the library whatever the
+    number of instances, and the other instances, which may have no data, are asked for no output."""
+    insts = [pk.Instance(fft_len=1 << 10, bits=8), pk.Instance(fft_len=1 << 9, bits=8), pk.Instance(fft_len=256, bits=2)]
+    plan = cpu_plan(*insts[:n])
+    packed = [torch.zeros(4096, dtype=torch.uint8)] + [None] * (n - 1)
+    gx, gy = torch.ones((1, 512), dtype=torch.complex64), torch.ones((1, 512), dtype=torch.complex64)
+    dt = torch.zeros((1, 2), dtype=torch.complex64)
+    out = autograd.stokes(plan, packed[0] if n == 1 else packed, gx, gy, dt, psi=0.25)
+    assert out.shape == (1, 4, 512) and out.dtype == torch.float32
+    (_, ptrs, counts, cal, outs), = recorder.named("ps_accumulate_stokes")
+    assert list(counts) == [2048] + [0] * (n - 1)
+    assert [ptrs[i] for i in range(n)] == [packed[0].data_ptr()] + [None] * (n - 1)
+    assert [outs[i] for i in range(n)] == [out.data_ptr()] + [None] * (n - 1)
+    assert (cal[0].gain_x, cal[0].gain_y, cal[0].dterms) == (gx.data_ptr(), gy.data_ptr(), dt.data_ptr())
+    assert cal[0].psi == 0.25
+    for i in range(1, n):
+        assert (cal[i].gain_x, cal[i].gain_y, cal[i].dterms, cal[i].psi) == (None, None, None, 0.0)

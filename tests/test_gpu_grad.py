@@ -229,3 +229,22 @@ def test_backward_argument_errors(env):
     with pytest.raises(pk.PolarisError) as e:
         rect.set_window_taps(torch.ones(64, device=dev))
     assert e.value.code == "PS_ERR_ARG"
+
+
+def test_forward_on_a_plan_of_several_instances(env):
+    """The differentiable forward on a plan of two instances: the calibrated Stokes of instance 0, bitwise as accumulate()
+    and stokes() give them, with and without data for the other instance."""
+    torch, pk, dev = env
+    from paper_1412_1256_amd import autograd
+    d = _case(1 << 13, 6, 77, taps=False)
+    other = synth.make_correlated_noise(2, 0.1, 1 << 14, 3, seed_extra=78)
+    packed = [torch.from_numpy(d["inst"]["packed"]).to(dev), torch.from_numpy(other["packed"]).to(dev)]
+    cal = {k: torch.from_numpy(d[v]).to(dev) for k, v in (("gain_x", "gx"), ("gain_y", "gy"), ("dterms", "dt"))}
+    plan = pk.Plan([pk.Instance.from_synth(d["inst"]), pk.Instance.from_synth(other)], device=dev)
+    for bufs in (packed, [packed[0], None]):
+        say(f"forward, second instance {'with' if bufs[1] is not None else 'without'} data")
+        got = autograd.stokes(plan, bufs, psi=d["psi"], **cal)
+        plan.reset()
+        plan.accumulate(bufs)
+        assert torch.equal(got, plan.stokes(0, psi=d["psi"], **cal))
+        assert not torch.equal(got, plan.stokes(0))

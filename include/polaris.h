@@ -283,8 +283,12 @@ ps_status ps_integration_id(ps_plan_t plan, int32_t inst, uint64_t* id);
 /* Integration state for checkpoint and resume: the accumulators and, for overlapped segmentation, the
  * samples waiting for the next call (the frame count is passed separately).  Device buffers of
  * ps_state_bytes bytes; export and import are enqueued on the plan's stream.  The accumulators are kept in the
- * layout of the instance's schedule (split, slots): a state belongs to plans of the same fields, schedule and
- * build of this library, since another build's defaults may differ. */
+ * layout of the instance's schedule (split, slots), which the buffer itself does not name and which may differ
+ * between builds: a state belongs to plans whose ps_state_layout (host only, with or without a workspace) gives
+ * the same eight numbers, so a caller that keeps states keeps these with them and compares them before an
+ * import.  They are a format number, fft_len, n_pairs, N1, N2, the slots, the frames that follow one another in a
+ * slot (4 with 16-bit passes, else 1) and the bytes of waiting samples. */
+ps_status ps_state_layout(ps_plan_t plan, int32_t inst, int64_t layout[8]);
 ps_status ps_state_bytes(ps_plan_t plan, int32_t inst, size_t* bytes);
 ps_status ps_state_export(ps_plan_t plan, int32_t inst, void* dst_dev, int64_t* n_frames);
 ps_status ps_state_import(ps_plan_t plan, int32_t inst, const void* src_dev, int64_t n_frames);

@@ -103,6 +103,7 @@ def lib():
             "ps_stokes": [vp, i32, C.POINTER(_Cal), vp],
             "ps_calibrate_backward": [vp, i32, vp, i64, C.POINTER(_Cal), vp, C.POINTER(_CalGrad)],
             "ps_state_bytes": [vp, i32, C.POINTER(sz)],
+            "ps_state_layout": [vp, i32, C.POINTER(i64)],
             "ps_state_export": [vp, i32, vp, C.POINTER(i64)],
             "ps_state_import": [vp, i32, vp, i64],
             "ps_unpack": [vp, i32, i32, i64, vp, vp],
@@ -437,22 +438,65 @@ class Plan:
         _check(lib().ps_set_window_taps(self._h, inst, _ptr(t)))
         self._taps_keepalive = t
 
-    def state_bytes(self, inst: int = 0) -> int:
-        n = C.c_size_t()
+    # A state is the library's buffer followed by the instance's layout, eight 64-bit integers (see ps_state_layout):
+    # states of different schedules can have the same size, and builds may differ in their defaults.
+    def _state_parts(self, inst: int):
+        n, layout = C.c_size_t(), (C.c_int64 * 8)()
         _check(lib().ps_state_bytes(self._h, inst, C.byref(n)))
-        return n.value
+        _check(lib().ps_state_layout(self._h, inst, layout))
+        return n.value, list(layout)
+
+    def state_bytes(self, inst: int = 0) -> int:
+        return self._state_parts(inst)[0] + 64
 
     def state_export(self, inst: int = 0):
-        buf = self.torch.empty(self.state_bytes(inst), dtype=self.torch.uint8, device=self.device)
+        size, layout = self._state_parts(inst)
+        buf = self.torch.empty(size + 64, dtype=self.torch.uint8, device=self.device)
         nf = C.c_int64()
         _check(lib().ps_state_export(self._h, inst, _ptr(buf), C.byref(nf)))
+        with self.torch.cuda.stream(self.stream):
+            tag = buf[size:].view(self.torch.int64)
+            for i, v in enumerate(layout):
+                tag[i].fill_(v)
         return buf, nf.value
 
     def state_import(self, buf, n_frames: int, inst: int = 0):
-        need = self.state_bytes(inst)
-        if buf is not None and buf.numel() * buf.element_size() < need:  # another schedule's state (or build's)
-            raise ValueError(f"instance {inst} has a state of {need} bytes, got {buf.numel() * buf.element_size()}")
+        """Take over a state of state_export().  One of another layout is refused (its layout is read from the device,
+        except while the plan's stream is being captured).  A state without a layout, from a build that wrote none, is
+        taken in the layout that such a build gave a plan of these fields and schedule."""
+        if buf is not None:
+            size, layout = self._state_parts(inst)
+            with self.torch.cuda.stream(self.stream):
+                flat = buf.reshape(-1).view(self.torch.uint8)
+                if flat.numel() != size + 64:
+                    flat = self._untagged_state(flat, size, layout, inst)
+                elif not (flat.is_cuda and self.torch.cuda.is_current_stream_capturing()):
+                    got = flat[size:].clone().view(self.torch.int64).tolist()
+                    if got != layout:
+                        raise ValueError(f"instance {inst} keeps its state as {layout[1:]}, got one of {got[1:]}")
+            buf = flat
         _check(lib().ps_state_import(self._h, inst, _ptr(buf), int(n_frames)))
+
+    def _untagged_state(self, flat, size, layout, inst):
+        _, _, _, _, n2, slots, block, waiting = layout
+        sched = (self.schedules[inst] if self.schedules else None) or Schedule()
+        if flat.numel() == size:
+            if n2 > 2048 and not sched.log2_n1:
+                raise ValueError(f"instance {inst}: a state without its layout may be one of 2048-point rows or of "
+                                 f"{n2}-point rows; name the split in the plan's schedule (log2_n1)")
+            return flat
+        # default plans once had half as many slots in a single pass, and one with 16-bit passes; the slots of such a
+        # state that this plan adds hold nothing
+        I = self.instances[inst]
+        single = I.fft_len <= 4096 and I.precision in ("fp32", 0) and sched.single_pass != 2
+        former = 1 if block > 1 else (slots // 2 if single and not sched.rowpass_slots else 0)
+        sums = (size - waiting) // slots * former
+        if not former or flat.numel() != sums + waiting:
+            raise ValueError(f"instance {inst} has a state of {size + 64} bytes, got {flat.numel()}")
+        full = self.torch.zeros(size, dtype=self.torch.uint8, device=flat.device)
+        full[:sums] = flat[:sums]
+        full[size - waiting:] = flat[sums:]
+        return full
 
     KERNELS = ("colpass", "rowpass", "stokes", "spectra", "backward", "other")
 

@@ -1568,6 +1568,9 @@ ps_status ps_calibrate_backward(ps_plan_t plan, int32_t inst, const void* packed
   return PS_OK;
 }
 
+// number of the accumulators' layout [slot][pair][unit][product][N2]; also what tells a tag from accumulator contents
+constexpr int64_t kStateFormat = 0x5053746174650001;
+
 ps_status ps_state_bytes(ps_plan_t plan, int32_t inst, size_t* bytes) {
   ps_status st = check_plan(plan, false);
   if (st != PS_OK) return st;
@@ -1575,6 +1578,23 @@ ps_status ps_state_bytes(ps_plan_t plan, int32_t inst, size_t* bytes) {
   if (!bytes) return fail(PS_ERR_ARG, "null bytes");
   const Inst& I = plan->inst[(size_t)inst];
   *bytes = I.acc_bytes() + (I.overlap() ? I.tail_bytes() : 0);
+  return PS_OK;
+}
+
+ps_status ps_state_layout(ps_plan_t plan, int32_t inst, int64_t layout[8]) {
+  ps_status st = check_plan(plan, false);
+  if (st != PS_OK) return st;
+  if ((st = check_inst(plan, inst)) != PS_OK) return st;
+  if (!layout) return fail(PS_ERR_ARG, "null layout");
+  const Inst& I = plan->inst[(size_t)inst];
+  layout[0] = kStateFormat;
+  layout[1] = I.N;
+  layout[2] = I.cfg.n_pairs;
+  layout[3] = I.N1;
+  layout[4] = I.N2;
+  layout[5] = I.G;
+  layout[6] = I.mx() ? 4 : 1;
+  layout[7] = I.overlap() ? (int64_t)I.tail_bytes() : 0;
   return PS_OK;
 }
 

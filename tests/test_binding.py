@@ -9,13 +9,20 @@ import paper_1412_1256_amd as pk
 from paper_1412_1256_amd import autograd
 
 
-class Recorder:
-    """Stands for the library: every function records its arguments and succeeds."""
+LIBRARY = pk.lib()
 
-    def __init__(self):
-        self.calls = []
+
+class Recorder:
+    """Stands for the library: every function records its arguments and succeeds, but for those
+    named real, which are the library's own."""
+
+    def __init__(self, real=()):
+        self.calls, self.real = [], real
 
     def __getattr__(self, name):
+        if name in self.real:
+            return getattr(LIBRARY, name)
+
         def call(*args):
             self.calls.append((name, args))
             return 0
@@ -81,3 +88,117 @@ def test_differentiable_stokes_calibrates_instance_0(recorder, n):
     assert cal[0].psi == 0.25
     for i in range(1, n):
         assert (cal[i].gain_x, cal[i].gain_y, cal[i].dterms, cal[i].psi) == (None, None, None, 0.0)
+
+
+@pytest.fixture
+def state_plan(monkeypatch):
+    """Unbound plans of one instance whose imports are recorded; sizes and layouts are the library's own."""
+    class Importer(Recorder):  # keeps the bytes that an import hands over (the buffer may live for the call only)
+        def ps_state_import(self, h, inst, ptr, frames):
+            n = C.c_size_t()
+            assert LIBRARY.ps_state_bytes(h, inst, C.byref(n)) == 0
+            got = torch.frombuffer(bytearray(C.string_at(ptr.value, n.value)), dtype=torch.uint8)
+            self.calls.append(("ps_state_import", (got, frames)))
+            return 0
+
+    r = Importer(real=("ps_state_bytes", "ps_state_layout", "ps_last_error"))
+    monkeypatch.setattr(pk, "lib", lambda: r)
+
+    def make(sched=None, **kw):
+        p = cpu_plan(pk.Instance(**kw))
+        p.stream, p.schedules, h, n = None, [sched], C.c_void_p(), C.c_size_t()
+        arr, sarr = (pk._Instance * 1)(p.instances[0].to_c()), (pk._Schedule * 1)((sched or pk.Schedule()).to_c())
+        assert LIBRARY.ps_plan_scheduled(arr, sarr, 1, C.byref(h), C.byref(n)) == 0, LIBRARY.ps_last_error()
+        p._h = h
+        return p
+
+    def taken(plan, buf):
+        """What state_import hands to the library: its bytes, or None when it refuses the state."""
+        before = len(r.named("ps_state_import"))
+        try:
+            plan.state_import(buf, 5)
+        except ValueError:
+            assert len(r.named("ps_state_import")) == before
+            return None
+        (got, frames), = r.named("ps_state_import")[before:]
+        assert frames == 5
+        return got
+
+    return make, taken  # (a plan's __del__ destroys its handle)
+
+
+def state_of(plan, tagged=True):
+    """A state as the plan would export it, every slot filled with its number plus one (waiting samples: 255)."""
+    size, layout = plan._state_parts(0)
+    slots, waiting = layout[5], layout[7]
+    buf = torch.full((size + 64 * tagged,), 255, dtype=torch.uint8)
+    buf[:size - waiting] = (torch.arange(slots) + 1).to(torch.uint8).repeat_interleave((size - waiting) // slots)
+    if tagged:
+        buf[size:] = torch.tensor(layout).view(torch.uint8)
+    return buf
+
+
+S = pk.Schedule
+STATE_PLANS = [(S(rowpass_slots=8), dict(fft_len=256)), (S(rowpass_slots=4), dict(fft_len=256)),
+               (S(rowpass_slots=16), dict(fft_len=256)), (S(5, rowpass_slots=8, single_pass=2), dict(fft_len=1 << 10)),
+               (S(4, rowpass_slots=8, single_pass=2), dict(fft_len=1 << 10)), (S(rowpass_slots=8), dict(fft_len=256, hop=128)),
+               (S(rowpass_slots=4), dict(fft_len=256, n_streams=3, pairs=((0, 1), (1, 2))))]
+
+
+@pytest.mark.parametrize("a", range(len(STATE_PLANS)))
+def test_state_is_taken_by_its_own_layout_only(state_plan, a):
+    """Slots (fewer and more), split at the same size, waiting samples and pairs: any other layout's state is refused."""
+    make, taken = state_plan
+    states = [state_of(make(s, **kw)) for s, kw in STATE_PLANS]
+    plan = make(STATE_PLANS[a][0], **STATE_PLANS[a][1])
+    for b, state in enumerate(states):
+        got = taken(plan, state)
+        assert (got is not None) == (a == b), (a, b)
+        if a == b:
+            assert torch.equal(got, state[:-64])
+    longer = torch.cat([states[a][:-64], torch.zeros(4096, dtype=torch.uint8)])
+    assert taken(plan, longer) is None and taken(plan, states[a][:-72]) is None
+
+
+def test_states_without_a_layout(state_plan):
+    """A buffer of the accumulators alone, as former builds wrote it: taken where its layout is certain."""
+    make, taken = state_plan
+    for sched, kw in STATE_PLANS:
+        plan = make(sched, **kw)
+        assert torch.equal(taken(plan, state_of(plan, tagged=False)), state_of(plan)[:-64])
+    # single pass by default: half of today's slots, the rest empty; the waiting samples stay at the end
+    for hop in (0, 1 << 11):
+        plan, half = make(fft_len=1 << 12, hop=hop), make(S(rowpass_slots=256), fft_len=1 << 12, hop=hop)
+        size, layout = plan._state_parts(0)
+        assert layout[5] == 512
+        old = state_of(half, tagged=False)
+        got = taken(plan, old)
+        sums = old.numel() - layout[7]
+        assert torch.equal(got[:sums], old[:sums]) and torch.equal(got[size - layout[7]:], old[sums:])
+        assert not got[sums:size - layout[7]].any()
+        assert taken(make(S(rowpass_slots=512), fft_len=1 << 12, hop=hop), old) is None  # slots named: not a default
+
+
+@pytest.mark.parametrize("log2n", [16, 18])
+def test_states_of_one_slot_16_bit_plans(state_plan, log2n):
+    make, taken = state_plan
+    plan = make(fft_len=1 << log2n, precision="fp16")
+    size, layout = plan._state_parts(0)
+    assert layout[5] > 1
+    old = torch.full((size // layout[5],), 7, dtype=torch.uint8)
+    got = taken(plan, old)
+    assert layout[6] == 4 and torch.equal(got[:old.numel()], old) and not got[old.numel():].any()
+    assert taken(plan, old[:-8]) is None
+
+
+def test_state_without_a_layout_of_long_rows(state_plan):
+    """2^21 points had 2048-point rows and have 4096-point rows at the same size: only a named split tells which."""
+    make, _ = state_plan
+    plan, named = make(fft_len=1 << 21), make(S(log2_n1=10), fft_len=1 << 21)
+    (size, layout), (size2, layout2) = plan._state_parts(0), named._state_parts(0)
+    assert size == size2 and layout[3:5] == [512, 4096] and layout2[3:5] == [1024, 2048]
+    buf = torch.empty(size, dtype=torch.uint8)
+    with pytest.raises(ValueError):
+        plan.state_import(buf, 5)
+    named.state_import(buf, 5)
+    assert len(pk.lib().named("ps_state_import")) == 1

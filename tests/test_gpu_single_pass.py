@@ -268,3 +268,62 @@ def test_state_of_fewer_slots_refused(env, slots):
     with pytest.raises(ValueError):
         plan.state_import(state, n)
     less.state_import(state, n)
+
+
+@pytest.mark.parametrize("log2n,precision,frames", [(12, "fp32", 700), (12, "fp32", 300), (16, "fp16", 41), (16, "fp16", 3)])
+def test_untagged_states_of_fewer_slots_resume(env, log2n, precision, frames):
+    """States without a layout in the slots that default plans once had (half as many in a single pass, one with 16-bit
+    passes), with every slot in use and with some unused: a resumed integration has the sums of an uninterrupted one
+    (FP64 additions in another order, at most frames x 2^-53 of a sum of like signs; the cross products by their
+    geometric mean power)."""
+    torch, pk, dev = env
+    say(f"N=2^{log2n} {precision}, {frames} frames before the export")
+    N, more = 1 << log2n, 5
+    inst = pk.Instance(fft_len=N, bits=8, precision=precision)
+    packed = torch.randint(0, 256, (2 * N * (frames + more),), dtype=torch.uint8, device=dev)
+    first, rest = packed[:2 * N * frames], packed[2 * N * frames:]
+    whole, plan = pk.Plan([inst], device=dev), pk.Plan([inst], device=dev)
+    whole.accumulate(first)
+    if precision == "fp32":
+        half = pk.Plan([inst], device=dev, schedules=[pk.Schedule(rowpass_slots=256)])
+        half.accumulate(first)
+        state, n = half.state_export()
+        old = state[:-64]
+    else:
+        state, n = whole.state_export()
+        slots = plan._state_parts(0)[1][5]
+        assert slots > 1
+        sums = state[:-64].view(torch.float64).view(slots, -1)[:min(slots, (frames + 3) // 4)]
+        old = sums.sum(0).contiguous().view(torch.uint8)
+    plan.state_import(old, n)
+    whole.accumulate(rest)
+    plan.accumulate(rest)
+    (want, nw), (got, ng) = whole.spectra(), plan.spectra()
+    assert nw == ng == frames + more
+    w, g = want[0], got[0]
+    scale = torch.stack((w[0], w[1], (w[0] * w[1]).sqrt(), (w[0] * w[1]).sqrt()))
+    assert float(((g - w).abs() / scale).max()) < 4 * nw * 2.0 ** -53
+
+
+def test_states_of_other_layouts_refused(env):
+    """More slots than the plan's, and the same size in another split, read back from the device."""
+    torch, pk, dev = env
+    inst = pk.Instance(fft_len=1 << 13, bits=8)
+    data = torch.randint(0, 256, (2 << 14,), dtype=torch.uint8, device=dev)
+    make = lambda *s: pk.Plan([inst], device=dev, schedules=[pk.Schedule(*s)])
+    wide, few, other = make(7, 0, 0, 0, 8), make(7, 0, 0, 0, 4), make(6, 0, 0, 0, 4)
+    states = []
+    for p in (wide, few, other):
+        p.accumulate(data)
+        states.append(p.state_export())
+    assert states[1][0].numel() == states[2][0].numel()
+    for i, p in enumerate((wide, few, other)):
+        for j, (state, n) in enumerate(states):
+            say(f"plan {i}, state {j}")
+            if i != j:
+                with pytest.raises(ValueError):
+                    p.state_import(state, n)
+        before = p.spectra()[0].clone()
+        p.reset()
+        p.state_import(*states[i])
+        assert torch.equal(p.spectra()[0], before)

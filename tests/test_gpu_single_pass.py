@@ -327,3 +327,21 @@ def test_states_of_other_layouts_refused(env):
         p.reset()
         p.state_import(*states[i])
         assert torch.equal(p.spectra()[0], before)
+
+
+@pytest.mark.parametrize("log2n,bound", [(8, 5.2e-8), (9, 5.1e-8), (10, 6.1e-8), (11, 6.5e-8), (12, 6.4e-8)])
+def test_rounding_of_constants_does_not_add_up(env, log2n, bound):
+    """Integrated power of white noise against 64 bits, rms over channels of the relative error.  Over many frames the
+    rounding of the data averages out and that of the transform's constants stays; the bounds are what an FP32 model of
+    passes of radix 8 leaves (a 16-point pass with every constant rounded to nearest leaves 6.6e-8 .. 9.7e-8)."""
+    torch, pk, dev = env
+    F = (1 << 21) >> log2n
+    inst = synth.make_correlated_noise(8, 0.3, 1 << log2n, F, seed_extra=900 + log2n)
+    acc, _, _, _ = oracle.run_instance(inst)
+    plan = pk.Plan([pk.Instance.from_synth(inst)], device=dev)
+    plan.accumulate(torch.from_numpy(inst["packed"]).to(dev))
+    got = plan.spectra()[0].cpu().numpy()
+    rel = (got[0, :2] - acc[0, :2]) / acc[0, :2]
+    e = float(np.sqrt(np.mean(rel[:, 1:] ** 2)))
+    say(f"N=2^{log2n}, {F} frames: {e:.2e}")
+    assert e < bound

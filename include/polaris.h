@@ -144,12 +144,13 @@ ps_status ps_plan(const ps_instance* inst, int32_t n_inst, ps_plan_t* out, size_
 
 /*
  * Schedule of one instance's passes (what the autotuner chooses; every field 0 = the default):
- *   log2_n1         the split N = N1 x N2 of the four-step transform (default floor(log2 N / 2); with FP32
- *                   passes 7, 8, 7, 8, 9 for 2^13 .. 2^17 points, 10 for 2^19, 9 for 2^20 and, unless
+ *   log2_n1         the split N = N1 x N2 of the four-step transform, N1 and N2 of 2^4 .. 2^11 points, N2 of 2^12
+ *                   for 2^21 and 2^22 points too (default floor(log2 N / 2); with FP32
+ *                   passes 7, 8, 7, 8, 9 for 2^13 .. 2^17 points, 9 for 2^19 (10 with 2- and 4-bit codes), 9 for 2^20 and, unless
  *                   colpass_cols or rowpass_frames is set, 9 and 10 for 2^21 and 2^22 points);
  *   colpass_cols    columns per column-pass workgroup (its LDS tile width and workgroup size);
  *   rowpass_frames  frames per row-pass workgroup batch (its workgroup size; default 8, 4 for 1024-point
- *                   rows, 2 for 2048, and 4 for 512-point rows once the row pass has 512 or more
+ *                   rows, 2 for 2048, 1 (no other) for 4096, and 4 for 512-point rows once the row pass has 512 or more
  *                   workgroups);
  *   col_wg_per_cu   column-pass workgroups per CU that the frame grouping aims at (1 .. 8; default 4 for
  *                   2^13, 2 for 2^14 .. 2^16 points with FP32 passes, else 1);

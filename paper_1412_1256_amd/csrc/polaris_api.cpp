@@ -388,6 +388,9 @@ int open_log2_n1(const ps_instance& c, const ps_schedule* s) {
   return default_log2_n1(c);
 }
 
+// largest row pass of a transform of 2^m points: rows of 4096 points run at 2^21 and 2^22
+int max_log2_n2(int m) { return m >= 21 ? 12 : 11; }
+
 int default_col_wgs(const ps_instance& c) {
   const int m = ilog2_exact(c.fft_len);
   if (c.precision != PS_PREC_FP32) return 1;
@@ -492,8 +495,8 @@ const char* schedule_error(const ps_instance& c, const ps_schedule& s, char* why
     }
     return nullptr;
   }
-  if (m1 < 4 || m1 > 11 || m2 < 4 || m2 > (s.log2_n1 ? 11 : 12)) {
-    snprintf(w, 160, "split 2^%d x 2^%d outside 2^4 .. 2^11 per pass", m1, m2);
+  if (m1 < 4 || m1 > 11 || m2 < 4 || m2 > max_log2_n2(m)) {
+    snprintf(w, 160, "split 2^%d x 2^%d: columns outside 2^4 .. 2^11 or rows outside 2^4 .. 2^%d", m1, m2, max_log2_n2(m));
     return w;
   }
   if (c.window == PS_WIN_TAPS && (m2 > 9 || m1 > 9)) {
@@ -937,10 +940,10 @@ ps_status ps_schedule_candidates(const ps_instance* inst, ps_schedule* out, int3
     }
     for (int m1 = m / 2 - 1; m1 <= m / 2 + 1; ++m1) {
       const int N1 = 1 << m1, N2 = 1 << (m - m1);
-      if (m1 < 4 || m - m1 < 4 || m1 > 11 || m - m1 > 11) continue;
+      if (m1 < 4 || m - m1 < 4 || m1 > 11 || m - m1 > max_log2_n2(m)) continue;
       const int G0 = default_slots(*inst, N1, N2);
       for (int cols = 4; cols <= 16; cols *= 2)
-        for (int fb = 2; fb <= 8; fb *= 2)
+        for (int fb = 1; fb <= 8; fb *= 2)  // (1: rows of 4096 points)
           for (int wg = 1; wg <= 4; wg *= 2)
             for (int G = std::max(1, G0 / 2); G <= std::min(64, 2 * G0); G *= 2) {
               const ps_schedule c{m1, cols, fb, wg, G, fused_eligible(*inst) ? 2 : 0};

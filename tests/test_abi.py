@@ -272,3 +272,35 @@ def test_instances_share_one_inter_pass_buffer():
     mixed = pk.plan_workspace_bytes([paper, pk.Instance(fft_len=1 << 20, bits=2), pk.Instance(fft_len=1 << 12)])
     t20 = 64 * (1 << 20) * 8  # 512 MiB: the largest chunk sets the buffer
     assert t20 <= mixed < t20 + 3 * (per_inst + (64 << 20))
+
+
+@pytest.mark.parametrize("log2n,log2n1,bits", [(21, 9, 8), (22, 10, 8), (21, 9, 2), (22, 10, 32)])
+def test_candidates_reach_the_default_of_long_transforms(log2n, log2n1, bits):
+    """2^21 and 2^22 points run in 4096-point rows by default: the split can be named, alone (the same plan) and with
+    tiles, and the candidates list it, so that a tuned plan is no slower than an untuned one; every candidate plans.
+    Shorter transforms have no such rows."""
+    inst = pk.Instance(fft_len=1 << log2n, bits=bits)
+
+    def plan(sched):
+        arr, sarr = (pk._Instance * 1)(inst.to_c()), (pk._Schedule * 1)(sched.to_c())
+        h, n = C.c_void_p(), C.c_size_t()
+        st = pk.lib().ps_plan_scheduled(arr, sarr, 1, C.byref(h), C.byref(n))
+        layout = (C.c_int64 * 8)()
+        if st == 0:
+            assert pk.lib().ps_state_layout(h, 0, layout) == 0
+            pk.lib().ps_destroy(h)
+        return st, n.value, list(layout)
+
+    assert plan(pk.Schedule())[2][3:5] == [1 << log2n1, 4096]
+    assert plan(pk.Schedule(log2n1)) == plan(pk.Schedule())
+    cands = pk.schedule_candidates(inst)
+    # (1024-point columns come in blocks of 8, 512-point ones in blocks of 16; one workgroup per CU, one slot)
+    assert pk.Schedule(log2n1, 16 if log2n1 == 9 else 8, 1, 1, 1) in cands
+    assert {c.log2_n1 for c in cands} == ({9, 10, 11} if log2n == 21 else {10, 11})  # (2^22 as 2^12 columns: never)
+    assert all(plan(c)[0] == 0 for c in cands)
+    assert all((c.rowpass_frames == 1) == (log2n - c.log2_n1 == 12) for c in cands)
+    assert pk.STATUS[plan(pk.Schedule(log2n1 - 1))[0]] == "PS_ERR_UNSUPPORTED"
+    short = pk.Instance(fft_len=1 << 20, bits=bits)
+    arr, sarr = (pk._Instance * 1)(short.to_c()), (pk._Schedule * 1)(pk.Schedule(8).to_c())
+    h, n = C.c_void_p(), C.c_size_t()
+    assert pk.STATUS[pk.lib().ps_plan_scheduled(arr, sarr, 1, C.byref(h), C.byref(n))] == "PS_ERR_UNSUPPORTED"

@@ -124,3 +124,31 @@ def test_tuner_cache(env, tmp_path, monkeypatch):
     assert autotune.best_schedule(inst, device=dev) == best
     plan = pk.Plan([inst], device=dev, tune=True)
     assert plan.schedules == [best]
+
+
+@pytest.mark.parametrize("log2n,log2n1", [(21, 9), (22, 10)])
+def test_candidates_of_4096_point_rows(env, log2n, log2n1):
+    """Every candidate of the default split of 2^21 and 2^22 points against the FP64 oracle, the default's own tiles
+    bitwise as the default."""
+    torch, pk, dev = env
+    F = 3
+    inst = synth.make_correlated_noise(8, 0.3, 1 << log2n, F, seed_extra=log2n + 40)
+    acc, nf, s2, _ = oracle.run_instance(inst)
+    ref = oracle.stokes(acc, nf, s2)
+    packed = torch.from_numpy(inst["packed"]).to(dev)
+
+    def run(s):
+        plan = pk.Plan([pk.Instance.from_synth(inst)], device=dev, schedules=[s])
+        plan.reset()
+        return plan.accumulate_stokes(packed)[0]
+
+    default = run(pk.Schedule())
+    cands = [c for c in pk.schedule_candidates(pk.Instance.from_synth(inst)) if c.log2_n1 == log2n1]
+    assert len(cands) >= 3
+    for s in cands:
+        got = run(s)
+        e = np.max(np.abs(got.cpu().numpy().astype(np.float64) - ref)) / np.mean(ref[:, 0, :])
+        say(f"  {s}: err {e:.2e}")
+        assert e < 1e-5, s
+    assert torch.equal(run(pk.Schedule(log2n1)), default)
+    assert torch.equal(run(pk.Schedule(log2n1, 16 if log2n1 == 9 else 8, 1, 1, 1)), default)

@@ -4,19 +4,22 @@ For one instance shape it enumerates the schedules the library can run (``ps_sch
 N = N1 x N2 split of the four-step transform, the column-pass tile width, the row-pass frames per batch, the
 column-pass frame grouping and the number of accumulator slots), times a whole integration with each of
 them on the device, and keeps the fastest in a JSON cache.  The cache is keyed by the instance's shape and
-format, the GPU architecture and the HIP version, and lives at $POLARIS_TUNE_CACHE (default
+format, the GPU architecture, the HIP version and the library's build (another build's kernels may favour another
+schedule), and lives at $POLARIS_TUNE_CACHE (default
 ~/.cache/paper_1412_1256_amd/tune.json).
 
 Every schedule computes the same spectra up to rounding; only speed differs.
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 import tempfile
 from dataclasses import asdict
 
-from . import Instance, Plan, Schedule, schedule_candidates
+from . import LIB_PATH, Instance, Plan, Schedule, schedule_candidates
 
 CACHE_ENV = "POLARIS_TUNE_CACHE"
 
@@ -26,12 +29,19 @@ def cache_path() -> str:
                                                      "tune.json")
 
 
+@functools.lru_cache(maxsize=None)
+def build_id(path: str = LIB_PATH) -> str:
+    """Digest of the library file: the same for the same build."""
+    with open(path, "rb") as f:
+        return hashlib.blake2b(f.read(), digest_size=8).hexdigest()
+
+
 def cache_key(instance: Instance, device) -> str:
     import torch
     props = torch.cuda.get_device_properties(device)
     arch = getattr(props, "gcnArchName", props.name)
     pairs = ",".join(f"{x}{y}" for x, y in instance.pairs)
-    return "|".join([arch, f"hip{torch.version.hip}", f"N{instance.fft_len}", f"bits{instance.bits}",
+    return "|".join([arch, f"hip{torch.version.hip}", f"lib{build_id()}", f"N{instance.fft_len}", f"bits{instance.bits}",
                      f"S{instance.n_streams}", f"pairs{pairs}", str(instance.window), str(instance.precision),
                      str(instance.accum), f"chunk{instance.chunk_frames}"])
 

@@ -1,12 +1,14 @@
 """Host side of the Python binding, on the CPU: what reaches the library for the tensors a caller may pass.  The
 library is replaced by a recorder, so nothing is launched."""
 import ctypes as C
+import json
+import types
 
 import pytest
 import torch
 
 import paper_1412_1256_amd as pk
-from paper_1412_1256_amd import autograd
+from paper_1412_1256_amd import autograd, autotune
 
 
 LIBRARY = pk.lib()
@@ -202,3 +204,27 @@ def test_state_without_a_layout_of_long_rows(state_plan):
         plan.state_import(buf, 5)
     named.state_import(buf, 5)
     assert len(pk.lib().named("ps_state_import")) == 1
+
+
+def test_tuned_schedules_belong_to_a_build(monkeypatch, tmp_path):
+    """A schedule tuned with another build of the library is not taken from the cache: it is timed again."""
+    inst, path = pk.Instance(fft_len=1 << 12), str(tmp_path / "tune.json")
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: types.SimpleNamespace(name="x", gcnArchName="gfx"))
+    monkeypatch.setattr(autotune, "_input_ring", lambda *a: [None])
+    ranked = []
+
+    def timing(instance, sched, *a, **k):
+        ranked.append(sched)
+        return abs(sched.rowpass_slots - best.rowpass_slots) + abs(sched.single_pass - best.single_pass)
+
+    monkeypatch.setattr(autotune, "time_schedule", timing)
+    for best in (pk.Schedule(6, 0, 0, 0, 64, 1), pk.Schedule(6, 0, 0, 0, 512, 1)):
+        monkeypatch.setattr(autotune, "build_id", lambda: f"build{best.rowpass_slots}")
+        assert autotune.best_schedule(inst, device="cpu", cache=path) == best
+        ranked.clear()
+        assert autotune.best_schedule(inst, device="cpu", cache=path) == best and not ranked
+    assert len(json.load(open(path))) == 2
+    monkeypatch.undo()
+    a, b = tmp_path / "a.so", tmp_path / "b.so"
+    a.write_bytes(b"one"), b.write_bytes(b"two")
+    assert autotune.build_id(str(a)) != autotune.build_id(str(b)) and len(autotune.build_id()) == 16

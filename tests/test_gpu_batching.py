@@ -281,3 +281,33 @@ def test_graph_errors(env):
         plan.accumulate(other)
     side.synchronize()
     assert plan.spectra(0)[1] == insts[0]["n_frames"]
+
+
+@pytest.mark.parametrize("frames", [8, 9, 20])
+def test_long_instance_leaves_the_others_grouped(env, frames):
+    """An instance of more than eight chunks in a call runs by itself; the others stay in one column-pass and one
+    row-pass launch per chunk round.  Spectra and Stokes bitwise as separate plans."""
+    torch, pk, dev = env
+    N = 1 << 13
+    data = [synth.make_precision(n_frames=frames, fft_len=N)]  # 4 streams, 2 pairs
+    data += [synth.make_correlated_noise(2, 0.2, N, 2, seed_extra=700 + i) for i in range(5)]
+    packed = [torch.from_numpy(d["packed"]).to(dev) for d in data]
+    insts = [pk.Instance.from_synth(d, chunk_frames=1 if i == 0 else 2, precision="fp32", accum="fp64")
+             for i, d in enumerate(data)]
+    plan = pk.Plan(insts, device=dev)
+    say(f"one instance of {frames} chunks, five of one")
+    plan.profile_enable(True)
+    plan.reset()
+    plan.accumulate(packed)
+    torch.cuda.synchronize(dev)
+    prof = plan.profile_read()
+    plan.profile_enable(False)
+    for k in ("colpass", "rowpass"):  # the first instance's format differs, so its launches are its own
+        assert prof[k][1] == frames + 1, prof
+    plan.reset()
+    st = plan.accumulate_stokes(packed)
+    for i, p in enumerate(packed):
+        one = pk.Plan([insts[i]], device=dev)
+        one.reset()
+        want = one.accumulate_stokes([p])[0]
+        assert torch.equal(plan.spectra(i)[0], one.spectra()[0]) and torch.equal(st[i], want), i

@@ -404,7 +404,8 @@ int default_col_wgs(const ps_instance& c) {
 
 // Frames of a pass pair: its fixed cost (first loads, last stores, set-up) is spread over many frames, while the
 // buffer between the passes should fit the last-level cache (256 MiB).  FP32 passes: 2^25 points of all pairs (a
-// 256 MiB buffer), at least 64 frames: 6-11 % faster than 2^24 points at 2^13 .. 2^18; two pairs of 2^25 points each
+// 256 MiB buffer) and, beyond 2^18 points, at least 64 frames (2^18 x 512 frames, four pairs, 2-bit codes: 2.30 ms in
+// chunks of 32, 2.55 of 64, 2.39 of 128; 2^19 x 256: 2.59 of 32 and 2.41 of 64): 6-11 % faster than 2^24 points at 2^13 .. 2^18; two pairs of 2^25 points each
 // are 10-14 % slower than of 2^24 (2^18 x 256 frames, 4-bit: 597 against 515 us; 2^16 x 1024: 540 and 481).  The window
 // adjoint takes the passes' buffer over when it holds the whole integration, so a learnable window keeps 2^25 points
 // a pair.  16-bit passes, whose workgroups sum and store per launch, gain more from long launches: 2^26 points a
@@ -413,7 +414,7 @@ int64_t default_chunk(const ps_instance& c) {
   int64_t points = int64_t(1) << 25;
   if (c.precision != PS_PREC_FP32) points *= 2;
   else if (c.window != PS_WIN_TAPS) points /= c.n_pairs;
-  return std::max<int64_t>(64, points / c.fft_len);
+  return std::max<int64_t>(c.fft_len <= (1 << 18) ? 32 : 64, points / c.fft_len);
 }
 
 // the single pass runs FP32 transforms of 2^8 .. 2^12 points

@@ -304,3 +304,14 @@ def test_candidates_reach_the_default_of_long_transforms(log2n, log2n1, bits):
     arr, sarr = (pk._Instance * 1)(short.to_c()), (pk._Schedule * 1)(pk.Schedule(8).to_c())
     h, n = C.c_void_p(), C.c_size_t()
     assert pk.STATUS[pk.lib().ps_plan_scheduled(arr, sarr, 1, C.byref(h), C.byref(n))] == "PS_ERR_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("log2n,pairs,frames", [(16, 1, 512), (16, 4, 128), (17, 3, 85), (18, 1, 128), (18, 2, 64),
+                                                (18, 3, 42), (18, 4, 32), (19, 1, 64), (19, 4, 64), (22, 4, 64)])
+def test_default_chunks_of_several_pairs(log2n, pairs, frames):
+    """The default inter-pass buffer holds 2^25 points of all pairs, beyond 2^18 points at least 64 frames: the workspace
+    is that of the same chunk named."""
+    ps = ((0, 1), (1, 2), (2, 3), (0, 3))[:pairs]
+    make = lambda c: pk.plan_workspace_bytes([pk.Instance(fft_len=1 << log2n, n_streams=4, pairs=ps, chunk_frames=c)])
+    assert make(0) == make(frames)
+    assert make(frames) - make(frames - 1) == pairs << (log2n + 3)

@@ -168,36 +168,48 @@ __device__ __forceinline__ void bspline4(double u, double (&b)[4]) {
   b[3] = u3 / 6.0;
 }
 
-// One wave per knot interval j: the interval's contributions to the normal equations, Gram entries G[q][p]
-// (q <= p, ten of them) of basis functions j + q, j + p and right-hand sides r[q].  Lane l adds the channels l,
-// l + 64, ... in order; the fourteen sums are then added over the lanes together (17 exchanges, where fourteen
-// whole-workgroup sums took 84 and 28 barriers).  Bound by latency: 832 intervals of 128 channels
-// in 3.8 us (one workgroup per interval 11.1 us).
-constexpr int kGramWaves = kNT / 64;
-
-__global__ void __launch_bounds__(kNT) k_spline_gram(SplineArgs a) {
-  const int lane = (int)threadIdx.x % 64;
-  const int64_t j = (int64_t)blockIdx.x * kGramWaves + threadIdx.x / 64;  // the same for a whole wave
+// W waves per knot interval j: the interval's contributions to the normal equations, Gram entries G[q][p]
+// (q <= p, ten of them) of basis functions j + q, j + p and right-hand sides r[q].  Lane l of the interval's 64 W adds the
+// channels l, l + 64 W, ... in order; the fourteen sums are then added over a wave's lanes together (17 exchanges, where
+// fourteen whole-workgroup sums took 84 and 28 barriers) and over the waves in order.  Bound by latency, of the lanes'
+// chains for wide intervals: see the launcher for W.  832 intervals of 128 channels in 3.8 us (11.1 us with fourteen
+// workgroup sums per interval).
+template <int W>
+__global__ void __launch_bounds__(W == 1 ? kNT : 64 * W) k_spline_gram(SplineArgs a) {
+  __shared__ double sh[14][W];
+  const int lane = (int)threadIdx.x % 64, wave = (int)threadIdx.x / 64;
+  const int64_t j = W == 1 ? (int64_t)blockIdx.x * (kNT / 64) + wave : (int64_t)blockIdx.x;  // the same for a whole wave
   if (j >= a.n_int) return;
   const int64_t lo = a.c0 + j * a.K;
   const int64_t hi = (lo + a.K) < a.c1 ? (lo + a.K) : a.c1;
   double g[16];  // fourteen sums and two zeros
 #pragma unroll
   for (int q = 0; q < 16; ++q) g[q] = 0.0;
-  for (int64_t c = lo + lane; c < hi; c += 64) {
+  for (int64_t c = lo + (W == 1 ? lane : (int)threadIdx.x); c < hi; c += 64 * W) {
     double b[4];
     bspline4((double)(c - lo) / (double)a.K, b);
     const double h = (double)a.h[c];
-    int k = 0;
+    int e = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int p = q; p < 4; ++p) g[k++] += b[q] * b[p];
+      for (int p = q; p < 4; ++p) g[e++] += b[q] * b[p];
 #pragma unroll
     for (int q = 0; q < 4; ++q) g[10 + q] += b[q] * h;
   }
   wave_sum16(g, lane);  // lane l holds value l / 4
-  if (lane % 4 == 0 && lane / 4 < 14) a.partial[j * 14 + lane / 4] = g[0];
+  if constexpr (W == 1) {
+    if (lane % 4 == 0 && lane / 4 < 14) a.partial[j * 14 + lane / 4] = g[0];
+  } else {
+    if (lane % 4 == 0 && lane / 4 < 14) sh[lane / 4][wave] = g[0];
+    __syncthreads();
+    if (threadIdx.x < 14) {
+      double v = 0.0;
+#pragma unroll
+      for (int k = 0; k < W; ++k) v += sh[threadIdx.x][k];
+      a.partial[j * 14 + threadIdx.x] = v;
+    }
+  }
 }
 
 // index of G[q][p] (q <= p) in an interval's ten Gram entries
@@ -1164,7 +1176,13 @@ hipError_t bandpass_scratch(hipStream_t stream, void** ptr) {
 }
 
 hipError_t launch_bandpass_fit(const SplineArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_spline_gram, dim3((unsigned)((a.n_int + kGramWaves - 1) / kGramWaves)), dim3(kNT), 0, s, a);
+  // Waves per interval: one up to 1024 channels (there the solve or, with thousands of intervals, the waves themselves
+  // fill the chip: 2^21 channels 44.9 us, 46.5 with four), four beyond (2^17 channels at 4096: 27.1 -> 17.0 us) and
+  // sixteen from 8192 on, where few intervals are left (16384: 73.2 us with one, 25.8 with four, 23.1 with sixteen).
+  const int W = a.K > 1024 ? (a.K < 8192 ? 4 : 16) : 1;
+  if (W == 1) hipLaunchKernelGGL(k_spline_gram<1>, dim3((unsigned)((a.n_int + kNT / 64 - 1) / (kNT / 64))), dim3(kNT), 0, s, a);
+  else if (W == 4) hipLaunchKernelGGL(k_spline_gram<4>, dim3((unsigned)a.n_int), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(k_spline_gram<16>, dim3((unsigned)a.n_int), dim3(1024), 0, s, a);
   // one thread per block of three coefficients (at most kMaxSplineCoef / 3), in whole waves
   const unsigned blocks = (unsigned)((a.n_coef + 2) / 3);
   hipLaunchKernelGGL(k_spline_solve, dim3(1), dim3((blocks + 63) / 64 * 64), 0, s, a);

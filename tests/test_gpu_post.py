@@ -320,3 +320,16 @@ def test_allan_side_by_side_sizes(env, P, n):
         say(f"allan side by side P={P} n={n} bad={bad}")
         got = pk.allan(torch.from_numpy(x).to(dev), lags, 0.5, normalize=bad, axis=0).cpu().numpy()
         rel_close(got, ref, 1e-10)
+
+
+@pytest.mark.parametrize("K,n_int,rest", [(1024, 4, 2), (1025, 4, 1000), (4096, 5, 2), (8191, 4, 300), (8192, 4, 0),
+                                          (8192, 4, 1025), (20000, 6, 777)])
+def test_bandpass_wide_knots(env, K, n_int, rest):
+    """Intervals of one, four and sixteen waves, with partial last intervals shorter than their lanes; NaN-free spectra,
+    FP32 output: half an ulp (6e-8) plus FP64 errors far below, bound 1e-6."""
+    torch, pk, dev = env
+    C = K * n_int + rest
+    h = spectra(1, C, 40 + K)[0]
+    say(f"{n_int} intervals of {K} channels and {rest}")
+    got = pk.bandpass_fit(torch.from_numpy(h).to(dev), K, 0.0).cpu().numpy()
+    rel_close(got, post.bandpass_fit(h, K, 0.0)[0], 1e-6)

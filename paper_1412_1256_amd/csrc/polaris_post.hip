@@ -32,12 +32,12 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return r;
 }
 
-// Sums over the wave of sixteen values at once: at each of four halving steps (lane distance 32, 16, 8, 4) a lane
-// gives away half of its values and adds its partner's other half, then two butterfly steps; lane l ends with the
-// sum of value l / 4 in g[0] (17 exchanges, a fixed order).
-template <int HALF = 8>
-__device__ __forceinline__ void wave_sum16(double (&g)[16], const int lane) {
-  constexpr int DIST = 4 * HALF;
+// Sums over the wave of V = 2, 4, 8 or 16 values at once: at each of log2 V halving steps (lane distance 32, 16, ...) a
+// lane gives away half of its values and adds its partner's other half, then butterfly steps; lane l ends with the
+// sum of value l / (64 / V) in g[0] (for sixteen values 17 exchanges; each value's order of additions does not depend on V).
+template <int V, int HALF = V / 2>
+__device__ __forceinline__ void wave_sums(double (&g)[V], const int lane) {
+  constexpr int DIST = HALF * 64 / V;
   const bool up = (lane & DIST) != 0;
 #pragma unroll
   for (int i = 0; i < HALF; ++i) {
@@ -45,10 +45,10 @@ __device__ __forceinline__ void wave_sum16(double (&g)[16], const int lane) {
     g[i] = keep + __shfl_xor(give, DIST, 64);
   }
   if constexpr (HALF > 1) {
-    wave_sum16<HALF / 2>(g, lane);
+    wave_sums<V, HALF / 2>(g, lane);
   } else {
-    g[0] += __shfl_xor(g[0], 2, 64);
-    g[0] += __shfl_xor(g[0], 1, 64);
+#pragma unroll
+    for (int o = 32 / V; o > 0; o >>= 1) g[0] += __shfl_xor(g[0], o, 64);
   }
 }
 
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(W == 1 ? kNT : 64 * W) k_spline_gram(SplineArg
 #pragma unroll
     for (int q = 0; q < 4; ++q) g[10 + q] += b[q] * h;
   }
-  wave_sum16(g, lane);  // lane l holds value l / 4
+  wave_sums<16>(g, lane);  // lane l holds value l / 4
   if constexpr (W == 1) {
     if (lane % 4 == 0 && lane / 4 < 14) a.partial[j * 14 + lane / 4] = g[0];
   } else {
@@ -472,17 +472,70 @@ __global__ void __launch_bounds__(kNT) k_allan_part(AllanArgs a, int64_t chunks)
 
 // The same partial sums for series of consecutive points (point_stride 1) whose lags are at most kWinMaxLag: the
 // workgroup stages its chunk with the largest lag's points on either side in LDS (points outside the series as
-// NaN) and one sweep serves eight lags.  A chunk whose staged points are all finite takes every term untested
+// NaN) and one sweep serves NL lags.  A chunk whose staged points are all finite takes every term untested
 // (its counts are known); any other tests each second difference.  Bound by FP64 issue, about ten operations a
-// term: 30 spectra of 131072 channels at 8 lags in
-// 19.3 us (37.6 us reading each term's three points from memory, lag by lag, with a workgroup sum per lag).
-constexpr int kChunkLags = 8;
+// term, so a call of few lags has a kernel of few: 30 spectra of 131072 channels at 8 lags in 19.3 us (37.6 us reading each
+// term's three points from memory, lag by lag, with a workgroup sum per lag); 300 spectra at one lag 127 us with the call
+// in a sweep of eight, 57 us in one of one.  (Registers: 96 for eight lags, 44 .. 60 for fewer; one kernel that picks the
+// sweep has 106 and is 5-7 % slower with eight lags.)
 
+// Lags l0 .. l0 + NL - 1 over the n points of a chunk staged at w + lmax.
+template <int NL>
+__device__ __forceinline__ void allan_sweep(const AllanArgs& a, const float* __restrict__ w, const int n, const int lmax,
+                                            const bool tested, const int l0, double* __restrict__ out,
+                                            double (&red)[kNT / 64][2 * NL]) {
+  const int tid = (int)threadIdx.x, lane = tid % 64;
+  int L[NL];
+  double v[2 * NL];  // sums, then counts
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    L[l] = l0 + l < a.n_lags ? a.lags[l0 + l] : 0;  // 0: not a lag of this group (a zero difference)
+    v[l] = v[NL + l] = 0.0;
+  }
+  if (!tested) {
+    for (int t = tid; t < n; t += kNT) {
+      const double xt = (double)w[lmax + t];
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
+        v[l] += d * d;
+      }
+    }
+  } else {
+    for (int t = tid; t < n; t += kNT) {
+      const double xt = (double)w[lmax + t];
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
+        const bool use = finite(d);
+        v[l] += use ? d * d : 0.0;
+        v[NL + l] += use ? 1.0 : 0.0;
+      }
+    }
+  }
+  // the sums over the wave (lane l then holds value l / (32 / NL)), then over the waves in order
+  wave_sums<2 * NL>(v, lane);
+  __syncthreads();  // the previous group's readers are done
+  if (lane % (32 / NL) == 0) red[tid / 64][lane / (32 / NL)] = v[0];
+  __syncthreads();
+  if (tid < NL && l0 + tid < a.n_lags) {
+    double s = 0.0, m = 0.0;
+#pragma unroll
+    for (int k = 0; k < kNT / 64; ++k) {
+      s += red[k][tid];
+      m += red[k][NL + tid];
+    }
+    out[2 * (l0 + tid)] = s;
+    out[2 * (l0 + tid) + 1] = tested ? m : (double)n;
+  }
+}
+
+template <int NL>
 __global__ void __launch_bounds__(kNT) k_allan_chunk(AllanArgs a, int64_t chunks, int lmax) {
   __shared__ float w[kAllanChunk + 2 * kWinMaxLag];
-  __shared__ double red[kNT / 64][2 * kChunkLags];
+  __shared__ double red[kNT / 64][2 * NL];
   __shared__ double sh[kNT / 64];
-  const int tid = (int)threadIdx.x, lane = tid % 64;
+  const int tid = (int)threadIdx.x;
   const int64_t s_ = blockIdx.x, c = blockIdx.y;
   const float* x = a.x + s_ * a.series_stride;
   const int64_t t0 = c * kAllanChunk;
@@ -525,51 +578,7 @@ __global__ void __launch_bounds__(kNT) k_allan_chunk(AllanArgs a, int64_t chunks
       out[2 * a.n_lags + 1] = m;
     }
   }
-  for (int l0 = 0; l0 < a.n_lags; l0 += kChunkLags) {
-    int L[kChunkLags];
-    double v[2 * kChunkLags];  // sums, then counts
-#pragma unroll
-    for (int l = 0; l < kChunkLags; ++l) {
-      L[l] = l0 + l < a.n_lags ? a.lags[l0 + l] : 0;  // 0: not a lag of this group (a zero difference)
-      v[l] = v[kChunkLags + l] = 0.0;
-    }
-    if (!tested) {
-      for (int t = tid; t < n; t += kNT) {
-        const double xt = (double)w[lmax + t];
-#pragma unroll
-        for (int l = 0; l < kChunkLags; ++l) {
-          const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
-          v[l] += d * d;
-        }
-      }
-    } else {
-      for (int t = tid; t < n; t += kNT) {
-        const double xt = (double)w[lmax + t];
-#pragma unroll
-        for (int l = 0; l < kChunkLags; ++l) {
-          const double d = (double)w[lmax + t + L[l]] - 2.0 * xt + (double)w[lmax + t - L[l]];
-          const bool use = finite(d);
-          v[l] += use ? d * d : 0.0;
-          v[kChunkLags + l] += use ? 1.0 : 0.0;
-        }
-      }
-    }
-    // sixteen sums over the wave by halving (lane l then holds value l / 4), then over the waves in order
-    wave_sum16(v, lane);
-    __syncthreads();  // the previous group's readers are done
-    if (lane % 4 == 0) red[tid / 64][lane / 4] = v[0];
-    __syncthreads();
-    if (tid < kChunkLags && l0 + tid < a.n_lags) {
-      double s = 0.0, m = 0.0;
-#pragma unroll
-      for (int k = 0; k < kNT / 64; ++k) {
-        s += red[k][tid];
-        m += red[k][kChunkLags + tid];
-      }
-      out[2 * (l0 + tid)] = s;
-      out[2 * (l0 + tid) + 1] = tested ? m : (double)n;
-    }
-  }
+  for (int l0 = 0; l0 < a.n_lags; l0 += NL) allan_sweep<NL>(a, w, n, lmax, tested, l0, out, red);
 }
 
 __global__ void __launch_bounds__(kNT) k_allan_total(AllanArgs a, int64_t chunks) {
@@ -1280,9 +1289,12 @@ hipError_t launch_allan(const AllanArgs& a, hipStream_t s) {
   } else {
     const int64_t chunks = a.n_points > 0 ? (a.n_points + kAllanChunk - 1) / kAllanChunk : 1;
     const dim3 grid((unsigned)a.n_series, (unsigned)chunks);
-    if (a.point_stride == 1 && lmax <= kWinMaxLag && a.n_points >= 1)
-      hipLaunchKernelGGL(k_allan_chunk, grid, dim3(kNT), 0, s, a, chunks, lmax);
-    else
+    if (a.point_stride == 1 && lmax <= kWinMaxLag && a.n_points >= 1) {
+      if (a.n_lags == 1) hipLaunchKernelGGL(k_allan_chunk<1>, grid, dim3(kNT), 0, s, a, chunks, lmax);
+      else if (a.n_lags == 2) hipLaunchKernelGGL(k_allan_chunk<2>, grid, dim3(kNT), 0, s, a, chunks, lmax);
+      else if (a.n_lags <= 4) hipLaunchKernelGGL(k_allan_chunk<4>, grid, dim3(kNT), 0, s, a, chunks, lmax);
+      else hipLaunchKernelGGL(k_allan_chunk<8>, grid, dim3(kNT), 0, s, a, chunks, lmax);
+    } else
       hipLaunchKernelGGL(k_allan_part, grid, dim3(kNT), 0, s, a, chunks);
     if (chunks >= kTotalChunks)
       hipLaunchKernelGGL(k_allan_total_wave, dim3((unsigned)a.n_series), dim3(kNT), 0, s, a, chunks);

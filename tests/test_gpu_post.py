@@ -333,3 +333,22 @@ def test_bandpass_wide_knots(env, K, n_int, rest):
     say(f"{n_int} intervals of {K} channels and {rest}")
     got = pk.bandpass_fit(torch.from_numpy(h).to(dev), K, 0.0).cpu().numpy()
     rel_close(got, post.bandpass_fit(h, K, 0.0)[0], 1e-6)
+
+
+@pytest.mark.parametrize("n_lags", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("bad", [0, 3])
+def test_allan_few_lags(env, n_lags, bad):
+    """Series of consecutive points at as many lags as each kernel of a sweep serves, and one more; FP64 sums in another
+    order: relative differences of order n eps, bound 1e-10."""
+    torch, pk, dev = env
+    rng = np.random.default_rng(n_lags)
+    x = (1 + 0.01 * rng.standard_normal((4, 40001))).astype(np.float32)
+    if bad:
+        x[1, rng.integers(0, 40001, bad)] = np.nan
+        x[3, :bad] = np.inf
+    lags = [1, 512, 3, 77, 256, 5, 2, 300, 8][:n_lags]
+    say(f"{n_lags} lags, bad={bad}")
+    for norm in (False, True):
+        ref = post.allan(x, lags, 2.0, norm)
+        got = pk.allan(torch.from_numpy(x).to(dev), lags, 2.0, normalize=norm, axis=1).cpu().numpy()
+        rel_close(got, ref, 1e-10)

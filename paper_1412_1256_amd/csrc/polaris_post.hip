@@ -1221,32 +1221,35 @@ hipError_t launch_band_stats(const float* x, int64_t n_spec, int64_t n_chan, dou
 // last round of phases better, while each run costs about as much as four more terms (its two first samples, its
 // bounds); the m with the least time for the rounds is taken, among those whose cut runs have an odd number of
 // terms, so that the runs of neighbouring phases start on different banks.
-static int series_runs(int64_t P, int64_t L, int ph) {
-  const int64_t M = P - 2 * L;
-  if (M < 2 * L) return 1;
-  const int64_t kf = M / L;
-  int64_t best = 1, cost = (L + ph - 1) / ph * (kf + 4);
-  for (int64_t m = 2; m <= kf && m <= 64; ++m) {
-    const int64_t q = kf / m, c = (L * m + ph - 1) / ph * (q + 4);
-    if (q % 2 == 1 && c < cost) {
+static int series_runs(int P, int L, int ph) {  // (P at most a few thousand: whole-series form)
+  if (L > P / 4) return 1;
+  const int kf = (P - 2 * L) / L;
+  int best = 1, cost = (L + ph - 1) / ph * (kf + 4);
+  for (int m = 2; m <= kf && m <= 64; ++m) {
+    const int q = kf / m;
+    if (q % 2 == 0) continue;
+    const int c = (L * m + ph - 1) / ph * (q + 4);
+    if (c < cost) {
       cost = c;
       best = m;
     }
   }
-  return (int)best;
+  return best;
 }
 
 // Series per workgroup of the whole-series form (0: too long): as many as fit half a CU's LDS, up to 64, so that
-// short series still make a workgroup's worth of work.
-static int series_per_block(int64_t P) {
-  for (int S = 64; S >= 8; S /= 2)
-    if (P * S * 4 <= kSeriesLdsBytes) return S;
-  return 0;
+// short series still make a workgroup's worth of work, but no more than leave 256 workgroups (2048 series of 100 points at
+// 8 lags: 14.9 us in 32 workgroups, 12.2 in 256, the rate of the call itself), or 128 of 8 series, whose rows are a
+// quarter of a cache line (4000 series of 1100 points: 18.7 us in 250 workgroups, 20.4 in 500).
+static int series_per_block(int64_t P, int64_t n_series) {
+  int S = 64;
+  while (S > 8 && (P * S * 4 > kSeriesLdsBytes || n_series <= (S > 16 ? 255 : 127) * S)) S /= 2;
+  return P * S * 4 <= kSeriesLdsBytes ? S : 0;
 }
 
 template <int S>
 static void launch_series(AllanArgs a, hipStream_t s) {
-  for (int l = 0; l < a.n_lags; ++l) a.runs[l] = series_runs(a.n_points, a.lags[l], kSeriesThreads / S);
+  for (int l = 0; l < a.n_lags; ++l) a.runs[l] = series_runs((int)a.n_points, a.lags[l], kSeriesThreads / S);
   const dim3 grid((unsigned)((a.n_series + S - 1) / S)), block(kSeriesThreads);
   const size_t lds = (size_t)a.n_points * S * 4;
   if (reinterpret_cast<uintptr_t>(a.x) % 16 == 0 && a.point_stride % 4 == 0 && a.n_series % 4 == 0)
@@ -1271,7 +1274,7 @@ hipError_t launch_allan(const AllanArgs& a, hipStream_t s) {
   for (int l = 0; l < a.n_lags; ++l) lmax = a.lags[l] > lmax ? a.lags[l] : lmax;
   const bool rows16 = reinterpret_cast<uintptr_t>(a.x) % 8 == 0 && a.point_stride % 2 == 0 && a.n_series % 2 == 0;
   const bool cols = allan_cols(a.n_series, a.point_stride, a.series_stride);
-  const int S = cols && a.n_points >= 1 ? series_per_block(a.n_points) : 0;
+  const int S = cols && a.n_points >= 1 ? series_per_block(a.n_points, a.n_series) : 0;
   if (S) {  // up to 2288 points
     switch (S) {
       case 64: launch_series<64>(a, s); break;

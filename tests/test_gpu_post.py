@@ -352,3 +352,24 @@ def test_allan_few_lags(env, n_lags, bad):
         ref = post.allan(x, lags, 2.0, norm)
         got = pk.allan(torch.from_numpy(x).to(dev), lags, 2.0, normalize=norm, axis=1).cpu().numpy()
         rel_close(got, ref, 1e-10)
+
+
+@pytest.mark.parametrize("P,n", [(5, 16320), (5, 16321), (100, 16324), (286, 16385), (287, 8160), (287, 8161), (572, 8164),
+                                 (573, 2032), (573, 2033), (1144, 2036), (1145, 2033)])
+def test_allan_widths_of_many_series(env, P, n):
+    """Enough side-by-side series for 64, 32 and 16 of them to a workgroup, and one group fewer; ragged last groups, odd
+    counts and non-finite samples.  Second differences of FP32 samples are exact in FP64 (not so those of samples divided by
+    their mean, hence not normalised); their sums in another order: of order P eps, bound 1e-10."""
+    torch, pk, dev = env
+    rng = np.random.default_rng(P + n)
+    x = (1 + 0.01 * rng.standard_normal((P, n))).astype(np.float32)
+    x[P // 2, 1] = np.nan
+    x[0, n - 1] = np.inf
+    x[:, n - 70] = -np.inf
+    lags = [1, 2, 7, 33, 64, 127, max(1, (P - 1) // 2), P // 2 + 1]
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        ref = post.allan(x.T, lags, 0.5)
+    say(f"allan side by side P={P} n={n}")
+    got = pk.allan(torch.from_numpy(x).to(dev), lags, 0.5, axis=0).cpu().numpy()
+    rel_close(got, ref, 1e-10)

@@ -93,45 +93,62 @@ __global__ void __launch_bounds__(kNT) k_chan_avg_span(ChanAvgArgs a) {
   }
 }
 
-// 64 <= factor <= kSpan: a wave per bin, straight from memory: lane j adds the channels j, j + 64, ... in order
-// (the loads of four such rounds issued together) and the 64 lane sums are added by a fixed butterfly.  Bound by
-// the read of the spectra: 30 spectra of 131072 channels at factor 256 in 8.2 us, 1.9 TB/s (11.2 us
-// staged in LDS first, with a barrier between the read and the sums).
+// 64 <= factor <= kSpan: a wave per NB bins, straight from memory: lane j adds the channels j, j + 64, ... of a bin in order
+// and the 64 lane sums are added by a fixed butterfly.  Four loads go out together, of NB bins, so that short bins keep as
+// many on their way as long ones.  Bound by the read of the spectra: 30 spectra of 131072 channels at factor 256 in
+// 8.2 us, 1.9 TB/s (11.2 us staged in LDS first, with a barrier between the read and the sums); 300 spectra at factor 64
+// 76 us with four bins, 137 us with one, at 100 57 us with two, 89 with one.
+template <int NB>
 __global__ void __launch_bounds__(kNT) k_chan_avg_wave(ChanAvgArgs a) {
+  constexpr int R = 4 / NB;  // loads of a bin that go out together
   const int64_t s = blockIdx.y;
   const int F = a.factor, lane = (int)threadIdx.x % 64;
   const int64_t n_bins = a.n_chan / F;
-  const int64_t b = (int64_t)blockIdx.x * (kNT / 64) + threadIdx.x / 64;  // the same for a whole wave
+  const int64_t b = ((int64_t)blockIdx.x * (kNT / 64) + threadIdx.x / 64) * NB;  // the same for a whole wave
   if (b >= n_bins) return;
   const float* row = a.in + s * a.n_chan + b * F;
   const uint8_t* flags = a.flags ? a.flags + b * F : nullptr;
-  double sum = 0.0;
-  int n = 0;
-  for (int i0 = lane; i0 < F; i0 += 256) {
-    float x[4];
-    bool use[4];
+  const int bins = n_bins - b < NB ? (int)(n_bins - b) : NB;
+  double sum[NB];
+  int n[NB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = i0 + 64 * j;
-      x[j] = i < F ? row[i] : NAN;
-      use[j] = !(flags && i < F && flags[i]);
-    }
+  for (int k = 0; k < NB; ++k) sum[k] = n[k] = 0;
+  for (int i0 = 0; i0 < F; i0 += 64 * R) {
+    float x[NB][R];
+    bool use[NB][R];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (use[j] && isfinite(x[j])) {
-        sum += (double)x[j];
-        ++n;
+    for (int k = 0; k < NB; ++k)
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int i = i0 + lane + 64 * j;
+        const bool in = i < F && k < bins;
+        x[k][j] = in ? row[k * F + i] : NAN;
+        use[k][j] = !(flags && in && flags[k * F + i]);
+      }
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const bool on = use[k][j] && isfinite(x[k][j]);
+        sum[k] += on ? (double)x[k][j] : 0.0;
+        n[k] += __popcll(__ballot(on));
       }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    sum += __shfl_xor(sum, o, 64);
-    n += __shfl_xor(n, o, 64);
+  for (int k = 0; k < NB; ++k) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum[k] += __shfl_xor(sum[k], o, 64);
+    if (lane == 0 && k < bins) {
+      a.out[s * n_bins + b + k] = n[k] ? (float)(sum[k] / n[k]) : NAN;
+      if (a.counts) a.counts[s * n_bins + b + k] = n[k];
+    }
   }
-  if (lane == 0) {
-    a.out[s * n_bins + b] = n ? (float)(sum / n) : NAN;
-    if (a.counts) a.counts[s * n_bins + b] = n;
-  }
+}
+
+template <int NB>
+static void launch_avg_wave(const ChanAvgArgs& a, int64_t n_bins, hipStream_t s) {
+  constexpr int per = kNT / 64 * NB;
+  hipLaunchKernelGGL(k_chan_avg_wave<NB>, dim3((unsigned)((n_bins + per - 1) / per), (unsigned)a.n_spec), dim3(kNT), 0, s, a);
 }
 
 // factor > kSpan: one workgroup per (spectrum, bin)
@@ -1143,8 +1160,9 @@ __global__ void __launch_bounds__(kWinThreads) k_allan_window(AllanArgs a) {
 hipError_t launch_channel_average(const ChanAvgArgs& a, hipStream_t s) {
   const int64_t n_bins = a.n_chan / a.factor;
   if (a.factor >= 64 && a.factor <= kSpan) {
-    const dim3 grid((unsigned)((n_bins + kNT / 64 - 1) / (kNT / 64)), (unsigned)a.n_spec);
-    hipLaunchKernelGGL(k_chan_avg_wave, grid, dim3(kNT), 0, s, a);
+    if (a.factor == 64) launch_avg_wave<4>(a, n_bins, s);
+    else if (a.factor <= 128) launch_avg_wave<2>(a, n_bins, s);
+    else launch_avg_wave<1>(a, n_bins, s);
   } else if (a.factor < 64) {
     const int nb = kSpan / a.factor;
     const dim3 grid((unsigned)((n_bins + nb - 1) / nb), (unsigned)a.n_spec);

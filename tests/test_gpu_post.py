@@ -373,3 +373,23 @@ def test_allan_widths_of_many_series(env, P, n):
     say(f"allan side by side P={P} n={n}")
     got = pk.allan(torch.from_numpy(x).to(dev), lags, 0.5, axis=0).cpu().numpy()
     rel_close(got, ref, 1e-10)
+
+
+@pytest.mark.parametrize("factor", [64, 65, 127, 128, 129])
+@pytest.mark.parametrize("bins", [1, 2, 3, 5, 16, 17])
+def test_channel_average_bins_of_a_wave(env, factor, bins):
+    """Bins that waves take in fours, twos and singly, in numbers that leave the last wave's group and the last workgroup
+    partly filled; flagged, non-finite and wholly flagged bins.  Counts exact, means within one FP32 rounding (1e-6)."""
+    torch, pk, dev = env
+    x = spectra(2, factor * bins, factor + bins)
+    x[1, ::7] = np.inf
+    flags = (np.arange(factor * bins) % 5 == 3).astype(np.uint8)
+    flags[(bins - 1) * factor:] = 1
+    for fl in (None, flags):
+        out, cnt = pk.channel_average(torch.from_numpy(x).to(dev), factor,
+                                      None if fl is None else torch.from_numpy(fl).to(dev))
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            ref, rcnt = post.channel_average(x, factor, fl)
+        assert np.array_equal(cnt.cpu().numpy(), rcnt)
+        rel_close(out.cpu().numpy(), ref, 1e-6)

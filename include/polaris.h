@@ -288,7 +288,7 @@ ps_status ps_integration_id(ps_plan_t plan, int32_t inst, uint64_t* id);
  * between builds: a state belongs to plans whose ps_state_layout (host only, with or without a workspace) gives
  * the same eight numbers, so a caller that keeps states keeps these with them and compares them before an
  * import.  They are a format number, fft_len, n_pairs, N1, N2, the slots, the frames that follow one another in a
- * slot (4 with 16-bit passes, else 1) and the bytes of waiting samples. */
+ * slot (16 with 16-bit passes, else 1) and the bytes of waiting samples. */
 ps_status ps_state_layout(ps_plan_t plan, int32_t inst, int64_t layout[8]);
 ps_status ps_state_bytes(ps_plan_t plan, int32_t inst, size_t* bytes);
 ps_status ps_state_export(ps_plan_t plan, int32_t inst, void* dst_dev, int64_t* n_frames);

@@ -469,7 +469,7 @@ class Plan:
             with self.torch.cuda.stream(self.stream):
                 flat = buf.reshape(-1).view(self.torch.uint8)
                 if flat.numel() != size + 64:
-                    flat = self._untagged_state(flat, size, layout, inst)
+                    flat = self._untagged_state(flat, size, layout, inst, int(n_frames))
                 elif not (flat.is_cuda and self.torch.cuda.is_current_stream_capturing()):
                     got = flat[size:].clone().view(self.torch.int64).tolist()
                     if got != layout:
@@ -477,25 +477,32 @@ class Plan:
             buf = flat
         _check(lib().ps_state_import(self._h, inst, _ptr(buf), int(n_frames)))
 
-    def _untagged_state(self, flat, size, layout, inst):
+    def _untagged_state(self, flat, size, layout, inst, n_frames):
         _, _, _, _, n2, slots, block, waiting = layout
         sched = (self.schedules[inst] if self.schedules else None) or Schedule()
-        if flat.numel() == size:
+        I, torch = self.instances[inst], self.torch
+        slot = (size - waiting) // slots
+        if block > 1:
+            # 16-bit passes: one slot, or as many as now in blocks of four frames; all slots' sums go into the first
+            former = 1 if flat.numel() != size else slots
+            used = max(1, min(former, -(-n_frames // 4)))
+        else:
+            # default plans once had half as many slots in a single pass; the slots that this plan adds hold nothing
+            single = I.fft_len <= 4096 and I.precision in ("fp32", 0) and sched.single_pass != 2
+            former = used = slots if flat.numel() == size else (slots // 2 if single and not sched.rowpass_slots else 0)
+        if not former or flat.numel() != former * slot + waiting:
+            raise ValueError(f"instance {inst} has a state of {size + 64} bytes, got {flat.numel()}")
+        if former == slots and (block == 1 or slots == 1):
             if n2 > 2048 and not sched.log2_n1:
                 raise ValueError(f"instance {inst}: a state without its layout may be one of 2048-point rows or of "
                                  f"{n2}-point rows; name the split in the plan's schedule (log2_n1)")
             return flat
-        # default plans once had half as many slots in a single pass, and one with 16-bit passes; the slots of such a
-        # state that this plan adds hold nothing
-        I = self.instances[inst]
-        single = I.fft_len <= 4096 and I.precision in ("fp32", 0) and sched.single_pass != 2
-        former = 1 if block > 1 else (slots // 2 if single and not sched.rowpass_slots else 0)
-        sums = (size - waiting) // slots * former
-        if not former or flat.numel() != sums + waiting:
-            raise ValueError(f"instance {inst} has a state of {size + 64} bytes, got {flat.numel()}")
-        full = self.torch.zeros(size, dtype=self.torch.uint8, device=flat.device)
-        full[:sums] = flat[:sums]
-        full[size - waiting:] = flat[sums:]
+        full = torch.zeros(size, dtype=torch.uint8, device=flat.device)
+        if block > 1:
+            full[:slot].view(torch.float64).copy_(flat[:used * slot].view(torch.float64).view(used, -1).sum(0))
+        else:
+            full[:used * slot] = flat[:used * slot]
+        full[size - waiting:] = flat[former * slot:]
         return full
 
     KERNELS = ("colpass", "rowpass", "stokes", "spectra", "backward", "other")

@@ -104,8 +104,9 @@ struct Inst {
   int64_t frames_in(int64_t T) const { return T < N ? 0 : (T - N) / hop + 1; }
   size_t slot_doubles() const { return (size_t)cfg.n_pairs * (size_t)(N1 / 2) * 4 * (size_t)N2; }
   size_t acc_bytes() const { return (size_t)G * slot_doubles() * sizeof(double); }
-  // slots that hold frames after F of them: frame by frame, in the 16-bit row pass in blocks of four
-  int slots_of(int64_t F) const { return (int)std::min<int64_t>(G, mx() ? (F + 3) / 4 : F); }
+  // slots that hold frames after F of them: frame by frame, in the 16-bit row pass in blocks
+  int slots_of(int64_t F) const { return (int)std::min<int64_t>(G, (F + slot_block() - 1) / slot_block()); }
+  int slot_block() const { return mx() ? ps::kMxBlock : 1; }
   int slots_used() const { return slots_of(n_frames); }
   // readers of more than kDirectSlots slots take their sum from a reduction into one slot
   size_t off_sumacc = 0, off_sumpart = 0;
@@ -789,6 +790,8 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   r.acc = ws_ptr<double>(plan, I.off_acc);
   r.G = I.G;
   r.F0 = I.n_frames;
+  r.b0 = (int32_t)(I.n_frames / ps::kMxBlock % I.G);
+  r.r0 = (int32_t)(I.n_frames % ps::kMxBlock);
   r.slot_stride = (int64_t)I.slot_doubles();
   // the stages scale Z by 1 / (16 * (N1 / 16) * 16) = 1 / (16 N1); products by its square
   r.unscale = std::ldexp(1.0, 2 * (4 + I.m1));
@@ -1603,7 +1606,7 @@ ps_status ps_state_layout(ps_plan_t plan, int32_t inst, int64_t layout[8]) {
   layout[3] = I.N1;
   layout[4] = I.N2;
   layout[5] = I.G;
-  layout[6] = I.mx() ? 4 : 1;
+  layout[6] = I.slot_block();
   layout[7] = I.overlap() ? (int64_t)I.tail_bytes() : 0;
   return PS_OK;
 }

@@ -92,13 +92,20 @@ struct MxColArgs {
                             // 3 int8 four streams as the pairs (0,2), (1,3), both in one workgroup
 };
 
+// Frames that follow one another in an accumulator slot of the 16-bit row pass (slot of frame a: a / kMxBlock mod G).  A
+// second slot is a second workgroup per unit, which pays from some twenty frames on (two int8 streams, 2^18 points: 8
+// frames 23.8 us in blocks of 16, 26.3 in blocks of 4, where they have two slots; 16 frames 31.3 and 32.3); blocks of 32
+// leave slots idle up to 64 frames (2^17 x 32: 32.6 us against 28.6).
+constexpr int kMxBlock = 16;
+
 struct MxRowArgs {
   const uint32_t* T;
   int32_t N1, P, n_frames;
   MxMats m;
   double* acc;              // [G][P][N1/2][4][N2] FP64, unscaled
-  int32_t G;                // accumulator slots
+  int32_t G;                // accumulator slots (a power of two)
   int64_t F0;               // frames accumulated since ps_reset before this launch
+  int32_t b0, r0;           // F0 = kMxBlock B + r0, r0 < kMxBlock, and b0 = B mod G
   int64_t slot_stride;      // doubles per slot
   double unscale;           // 1 / (product scale)^2 of the stages: multiplies the sums before they are stored
 };

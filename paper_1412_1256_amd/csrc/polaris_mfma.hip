@@ -297,9 +297,8 @@ __global__ void __launch_bounds__(256, 2) k_colpass_mx(MxColArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // row pass: a workgroup owns one unit (rows k1 and N1 - k1, or 0 and N1/2) of one pair and one accumulator slot g of
-// G; wave w takes the absolute frames a = 4 b + w of the blocks b with b mod G = g, so that short integrations use
-// one slot.  For each row, stage A (vectors b = 16h + n) goes through a wave-private LDS
-// exchange to stage B (vectors kappa); the spectra of both rows go to LDS, and each lane forms XX*, YY*,
+// G: the absolute frames of the blocks of kMxBlock frames whose number is g mod G, every fourth of a block to a wave.
+// For each row, stage A (vectors b = 16h + n) goes through a wave-private LDS exchange to stage B (vectors kappa); the spectra of both rows go to LDS, and each lane forms XX*, YY*,
 // XY* of its channel slots and integrates them in registers.  At the end the four waves' sums are added in
 // wave order, unscaled (an exact power of two) and stored into the FP64 accumulators.
 // ------------------------------------------------------------------------------------------------
@@ -319,13 +318,21 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform
   const int u = (int)blockIdx.x, p = (int)blockIdx.y;
   const int N1 = a.N1, U = N1 / 2;
-  // frames of the launch, f = a - F0, in this slot: from f0 on, every NW G-th one (f0 < 0: a frame before the launch)
+  // Frames of the launch, f = a - F0, in this slot: blocks of kMxBlock frames from f = s0 (negative when the first began
+  // before the launch) on, G blocks apart, wave w takes every fourth frame of a block; q counts these.
   const int gs = (int)blockIdx.z;
-  const int64_t b0 = a.F0 / NW, bf = b0 + (gs - b0 % a.G + a.G) % a.G;
-  if (bf * NW - a.F0 >= a.n_frames) return;  // (bf >= F0 / NW, so otherwise some wave has a frame)
-  int f0 = (int)(bf * NW - a.F0) + w;
-  const int fs = NW * a.G;
-  if (f0 < 0) f0 += fs;
+  const int s0 = ((gs - a.b0) & (a.G - 1)) * kMxBlock - a.r0;
+  if (s0 >= a.n_frames) return;  // (s0 > -kMxBlock, so otherwise some wave has a frame)
+  constexpr int QN = kMxBlock / NW;
+  auto step = [&](int& f, int& q) {
+    f += NW;
+    if (++q == QN) {
+      q = 0;
+      f += kMxBlock * (a.G - 1);
+    }
+  };
+  int f0 = s0 + w, q0 = 0;
+  while (f0 < 0) step(f0, q0);
   const int rows[2] = {u == 0 ? 0 : u, u == 0 ? N1 / 2 : N1 - u};
   uint32_t* X = reinterpret_cast<uint32_t*>(lds + w * WAVE_BYTES);
   float2* spec = reinterpret_cast<float2*>(lds + w * WAVE_BYTES + H * 16 * XS * 4);
@@ -368,7 +375,7 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   // prefetches are unconditional (past the end a wave fetches its last frame again), so each frame waits
   // only for its own loads and the next frame's stay in flight
   if (f0 < a.n_frames) fetch(f0);
-  for (int f = f0; f < a.n_frames; f += fs) {
+  for (int f = f0, q = q0; f < a.n_frames;) {
     uint32_t cur[2][H][4];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
@@ -376,7 +383,9 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
       for (int h = 0; h < H; ++h)
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) cur[r][h][jj] = raw[r][h][jj];
-    fetch(f + fs < a.n_frames ? f + fs : f);
+    int fn = f, qn = q;
+    step(fn, qn);
+    fetch(fn < a.n_frames ? fn : f);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       f4v o[H][2];
@@ -438,6 +447,8 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
       }
     }
     wave_sync();
+    f = fn;
+    q = qn;
   }
   // ---- combine the waves' sums in wave order
   __syncthreads();
@@ -452,7 +463,7 @@ __global__ void __launch_bounds__(256, 2) k_rowpass_mx(MxRowArgs a) {
   __syncthreads();
   if (w == 0) {
     double* acc = a.acc + gs * a.slot_stride + (int64_t)(p * U + u) * 4 * N2;
-    const bool first = a.F0 <= (int64_t)NW * gs;  // the slot holds no frame of this integration yet
+    const bool first = a.F0 <= (int64_t)kMxBlock * gs;  // the slot holds no frame of this integration yet
 #pragma unroll
     for (int m = 0; m < SPL; ++m) {
       const int s = lane + 64 * m;

@@ -114,16 +114,16 @@ def state_plan(monkeypatch):
         p._h = h
         return p
 
-    def taken(plan, buf):
+    def taken(plan, buf, n=5):
         """What state_import hands to the library: its bytes, or None when it refuses the state."""
         before = len(r.named("ps_state_import"))
         try:
-            plan.state_import(buf, 5)
+            plan.state_import(buf, n)
         except ValueError:
             assert len(r.named("ps_state_import")) == before
             return None
         (got, frames), = r.named("ps_state_import")[before:]
-        assert frames == 5
+        assert frames == n
         return got
 
     return make, taken  # (a plan's __del__ destroys its handle)
@@ -181,16 +181,24 @@ def test_states_without_a_layout(state_plan):
         assert taken(make(S(rowpass_slots=512), fft_len=1 << 12, hop=hop), old) is None  # slots named: not a default
 
 
+@pytest.mark.parametrize("frames", [1, 4, 5, 9, 1000])
 @pytest.mark.parametrize("log2n", [16, 18])
-def test_states_of_one_slot_16_bit_plans(state_plan, log2n):
+def test_untagged_states_of_16_bit_plans(state_plan, log2n, frames):
+    """One slot, or the plan's number of slots in blocks of four frames (of which a short integration used the first):
+    the sums of all used slots, in the first."""
     make, taken = state_plan
     plan = make(fft_len=1 << log2n, precision="fp16")
     size, layout = plan._state_parts(0)
-    assert layout[5] > 1
-    old = torch.full((size // layout[5],), 7, dtype=torch.uint8)
-    got = taken(plan, old)
-    assert layout[6] == 4 and torch.equal(got[:old.numel()], old) and not got[old.numel():].any()
-    assert taken(plan, old[:-8]) is None
+    slots, slot = layout[5], size // layout[5]
+    assert slots > 1 and layout[6] > 1
+    for former in (1, slots):
+        sums = torch.rand(former, slot // 8, dtype=torch.float64)
+        used = min(former, (frames + 3) // 4)
+        sums[used:] = float("nan")  # never written
+        old = sums.reshape(-1).view(torch.uint8)
+        got = taken(plan, old, frames).view(torch.float64).view(slots, -1)
+        assert torch.equal(got[0], sums[:used].sum(0)) and not got[1:].any()
+        assert taken(plan, old[:-8], frames) is None
 
 
 def test_state_without_a_layout_of_long_rows(state_plan):

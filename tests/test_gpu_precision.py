@@ -203,3 +203,31 @@ def test_slots_and_windowed_words(env, log2n, streams, F, cuts, window):
     scale = got[:, :2].mean(dim=2).amax()
     assert nf == F
     assert float((got - one).abs().max() / scale) < 1e-6 and float((items - one).abs().max() / scale) < 1e-6
+
+
+@pytest.mark.parametrize("log2n,streams,F,cuts", [(16, 2, 3, ()), (16, 2, 16, (5,)), (16, 2, 17, (16,)), (16, 2, 33, (15, 32)),
+                                                  (16, 2, 83, (1, 18, 64)), (17, 4, 37, (20, 21)), (18, 2, 50, (31,))])
+def test_slot_blocks_sum_every_frame_once(env, log2n, streams, F, cuts):
+    """The 16-bit row pass's slots in blocks of sixteen frames: integrations shorter and longer than a block and than all
+    slots' blocks, calls that begin and end inside one.  Against the frames integrated one by one, whose spectra are
+    added in FP64: the same products, so the sums differ by their order only (F x 2^-53 of the terms' sizes)."""
+    torch, pk, dev = env
+    N = 1 << log2n
+    pairs = ((0, 1),) if streams == 2 else ((0, 2), (1, 3))
+    plan = pk.Plan([pk.Instance(fft_len=N, bits=8, n_streams=streams, pairs=pairs, precision="fp16")], device=dev)
+    gen = torch.Generator(device=dev).manual_seed(F)
+    data = (torch.randn((F, N * streams), device=dev, generator=gen) * 16).clamp(-127, 127).to(torch.int8).view(torch.uint8)
+    say(f"N=2^{log2n} streams={streams} F={F} cuts={cuts}")
+    want = torch.zeros((len(pairs), 4, N // 2), dtype=torch.float64, device=dev)
+    for f in range(F):
+        plan.reset()
+        plan.accumulate(data[f])
+        want += plan.spectra()[0]
+    steps = (0,) + cuts + (F,)
+    plan.reset()
+    for lo, hi in zip(steps, steps[1:]):
+        plan.accumulate(data[lo:hi].reshape(-1))
+    got, n = plan.spectra()
+    cross = (want[:, 0] * want[:, 1]).sqrt()[:, None]
+    size = torch.cat((want[:, :2], cross, cross), 1)
+    assert n == F and float(((got - want).abs() / size).max()) < 4 * F * 2.0 ** -53

@@ -293,7 +293,7 @@ def test_untagged_states_of_fewer_slots_resume(env, log2n, precision, frames):
         state, n = whole.state_export()
         slots = plan._state_parts(0)[1][5]
         assert slots > 1
-        sums = state[:-64].view(torch.float64).view(slots, -1)[:min(slots, (frames + 3) // 4)]
+        sums = state[:-64].view(torch.float64).view(slots, -1)[:min(slots, -(-frames // plan._state_parts(0)[1][6]))]
         old = sums.sum(0).contiguous().view(torch.uint8)
     plan.state_import(old, n)
     whole.accumulate(rest)

@@ -76,6 +76,8 @@ struct Inst {
   // column-pass workgroups per CU aimed at by the frame grouping
   int cols = 0, fb = 0, col_wgs = 1;
   int G = 1;  // accumulator slots (row-pass frame groups)
+  int g = 1;  // of these, in use by the current integration (set by its first accumulate)
+  int g_hist = 1;  // in use while histograms are counted
   // single pass: whole frames transformed in LDS (short FP32 transforms), with the table W_N^m, m < N
   bool fused = false;
   size_t off_tw_full = 0;
@@ -105,7 +107,7 @@ struct Inst {
   size_t slot_doubles() const { return (size_t)cfg.n_pairs * (size_t)(N1 / 2) * 4 * (size_t)N2; }
   size_t acc_bytes() const { return (size_t)G * slot_doubles() * sizeof(double); }
   // slots that hold frames after F of them: frame by frame, in the 16-bit row pass in blocks
-  int slots_of(int64_t F) const { return (int)std::min<int64_t>(G, (F + slot_block() - 1) / slot_block()); }
+  int slots_of(int64_t F) const { return (int)std::min<int64_t>(g, (F + slot_block() - 1) / slot_block()); }
   int slot_block() const { return mx() ? ps::kMxBlock : 1; }
   int slots_used() const { return slots_of(n_frames); }
   // readers of more than kDirectSlots slots take their sum from a reduction into one slot
@@ -151,6 +153,7 @@ struct ps_plan_s {
   struct InstState {
     bool first, hist_zeroed;
     int64_t n_frames, hist_frames;
+    int g;
   };
   std::vector<InstState> graph_state;
   uint64_t gen_counter = 0;
@@ -439,6 +442,15 @@ int default_slots_fused(const ps_instance& c) {
   return G;
 }
 
+// Slots of an integration with histograms, which runs the four-step passes: their row pass walks several frames per slot
+// best (two int8 streams, 2^22 samples: 2^12 points 53 us with 64 slots, 63 with 256, 77 with the single pass's 512;
+// 2^10 points 83 us with 256, 89 with 1024, 104 with 2048).
+int hist_slots(const ps_instance& c, int G) {
+  const int64_t target = (int64_t(1) << 18) / c.fft_len / c.n_pairs;
+  while (G > 1 && G > target) G /= 2;
+  return G;
+}
+
 // Accumulator slots: enough row-pass frame groups that units x pairs x slots reach about 512 workgroups for
 // frames of at most 2^18 points and 256 beyond (twice the slots measured faster up to 2^18).  The 16-bit row pass,
 // whose workgroups of four waves share a CU in twos, needs 512 of them as well (two int8 streams, one pair,
@@ -581,7 +593,7 @@ ps::RowArgs row_args(ps_plan_t plan, const Inst& I, int nf, int64_t F0) {
   ra.n_frames = nf;
   ra.tw_row = ws_ptr<float2>(plan, I.off_tw_row);
   ra.acc = ws_ptr<double>(plan, I.off_acc);
-  ra.G = I.G;
+  ra.G = I.g;
   ra.F0 = F0;
   ra.slot_stride = (int64_t)I.slot_doubles();
   return ra;
@@ -788,9 +800,9 @@ ps_status accumulate_mx(ps_plan_t plan, Inst& I, const ps::ColArgs& ca) {
   r.m.aR = ws_ptr<uint32_t>(plan, I.N2 == 512 ? I.off_mx32 : I.off_mx16);
   r.m.tws = ws_ptr<float2>(plan, I.off_tws_row);
   r.acc = ws_ptr<double>(plan, I.off_acc);
-  r.G = I.G;
+  r.G = I.g;
   r.F0 = I.n_frames;
-  r.b0 = (int32_t)(I.n_frames / ps::kMxBlock % I.G);
+  r.b0 = (int32_t)(I.n_frames / ps::kMxBlock % I.g);
   r.r0 = (int32_t)(I.n_frames % ps::kMxBlock);
   r.slot_stride = (int64_t)I.slot_doubles();
   // the stages scale Z by 1 / (16 * (N1 / 16) * 16) = 1 / (16 N1); products by its square
@@ -862,7 +874,7 @@ ps_status run_frames(ps_plan_t plan, Inst& I, const uint8_t* base, int64_t F, bo
       fa.win = ws_ptr<float>(plan, I.off_win);  // a table of ones for the rectangular window
       fa.tw = ws_ptr<float2>(plan, I.off_tw_full);
       fa.acc = ws_ptr<double>(plan, I.off_acc);
-      fa.G = I.G;
+      fa.G = I.g;
       fa.N1 = (int32_t)I.N1;
       fa.N2 = (int32_t)I.N2;
       fa.F0 = I.n_frames;
@@ -1000,6 +1012,8 @@ ps_status ps_plan_scheduled(const ps_instance* inst, const ps_schedule* sched, i
     I.fused = uses_fused(I.cfg, sched ? &sched[i] : nullptr);
     I.G = (sched && sched[i].rowpass_slots && !I.mx()) ? sched[i].rowpass_slots
                                              : (I.fused ? default_slots_fused(I.cfg) : default_slots(I.cfg, (int)I.N1, (int)I.N2));
+    I.g = I.G;
+    I.g_hist = I.fused && !(sched && sched[i].rowpass_slots) ? hist_slots(I.cfg, I.G) : I.G;
     I.fb = (sched && sched[i].rowpass_frames) ? sched[i].rowpass_frames
                                               : default_rowpass_frames(I.cfg, (int)I.N1, (int)I.N2, (int)I.G);
     I.chunk = inst[i].chunk_frames ? inst[i].chunk_frames : default_chunk(I.cfg);
@@ -1180,8 +1194,12 @@ static int64_t frames_after(const Inst& I, int64_t T) {
 
 static ps_status accumulate_impl(ps_plan_t plan, const void* const* packed_dev, const int64_t* n_samples) {
   ps_status st = PS_OK;
-  for (size_t i = 0; i < plan->inst.size(); ++i)
-    if (n_samples[i] > 0) plan->touch(plan->inst[i]);
+  for (size_t i = 0; i < plan->inst.size(); ++i) {
+    Inst& I = plan->inst[i];
+    if (n_samples[i] == 0) continue;
+    plan->touch(I);
+    if (I.n_frames == 0) I.g = I.hist_on ? I.g_hist : I.G;
+  }
   // First, per instance: the histogram clear and, with overlapped frames, the frames that span the
   // previous call and this one (they precede this call's own frames in the integration).
   for (size_t i = 0; i < plan->inst.size(); ++i) {
@@ -1409,7 +1427,7 @@ ps_status ps_graph_end(ps_plan_t plan, int32_t keep) {
   if (plan->gexec) (void)hipGraphExecDestroy(plan->gexec);
   plan->gexec = x;
   plan->graph_state.clear();
-  for (const Inst& I : plan->inst) plan->graph_state.push_back({I.first, I.hist_zeroed, I.n_frames, I.hist_frames});
+  for (const Inst& I : plan->inst) plan->graph_state.push_back({I.first, I.hist_zeroed, I.n_frames, I.hist_frames, I.g});
   return PS_OK;
 }
 
@@ -1427,6 +1445,7 @@ ps_status ps_graph_launch(ps_plan_t plan) {
     I.n_frames = g.n_frames;
     I.hist_zeroed = g.hist_zeroed;
     I.hist_frames = g.hist_frames;
+    I.g = g.g;
     plan->touch(I);
   }
   return PS_OK;
@@ -1618,7 +1637,11 @@ ps_status ps_state_export(ps_plan_t plan, int32_t inst, void* dst_dev, int64_t* 
   const Inst& I = plan->inst[(size_t)inst];
   if (!dst_dev) return fail(PS_ERR_ARG, "null destination");
   if (I.n_frames == 0) return fail(PS_ERR_STATE, "instance %d has no accumulated frames", inst);
-  hipError_t e = ps::launch_copy(plan->ws + I.off_acc, dst_dev, I.acc_bytes(), plan->stream);
+  const size_t used = (size_t)I.g * I.slot_doubles() * sizeof(double);
+  hipError_t e = ps::launch_copy(plan->ws + I.off_acc, dst_dev, used, plan->stream);
+  if (e == hipSuccess && used < I.acc_bytes())  // slots that this integration does not use hold nothing
+    e = ps::launch_zero_u64(reinterpret_cast<unsigned long long*>(static_cast<char*>(dst_dev) + used),
+                            (int64_t)((I.acc_bytes() - used) / 8), plan->stream);
   if (e == hipSuccess && I.overlap())
     e = ps::launch_copy(plan->ws + I.off_stage, static_cast<char*>(dst_dev) + I.acc_bytes(), I.tail_bytes(), plan->stream);
   if (e != hipSuccess) return hip_fail(e, "state export");
@@ -1638,6 +1661,7 @@ ps_status ps_state_import(ps_plan_t plan, int32_t inst, const void* src_dev, int
     e = ps::launch_copy(static_cast<const char*>(src_dev) + I.acc_bytes(), plan->ws + I.off_stage, I.tail_bytes(), plan->stream);
   if (e != hipSuccess) return hip_fail(e, "state import");
   I.n_frames = n_frames;
+  I.g = I.G;
   I.first = false;
   plan->touch(I);
   return PS_OK;

@@ -120,3 +120,56 @@ def test_histograms_read_separately(env, bits):
     torch.cuda.synchronize(dev)
     assert torch.equal(only_c, counts) and torch.equal(only_p.nan_to_num(-1.0), power.nan_to_num(-1.0))
     assert int(counts.sum()) == 4 * N * F
+
+
+@pytest.mark.parametrize("log2n,F,pairs", [(8, 1500, 1), (9, 40, 1), (10, 300, 1), (11, 70, 2), (12, 200, 1), (12, 600, 2)])
+def test_slots_of_counted_integrations(env, log2n, F, pairs):
+    """Integrations of short transforms with histograms use fewer accumulator slots than those without.  Spectra against
+    the FP64 oracle (1e-5 of the mean power), split calls bitwise; a state exported with fewer slots in use resumes in a
+    plan that uses all (FP64 sums in another order, 1e-12); a captured integration with histograms is read in its own
+    slots after integrations without."""
+    torch, pk, dev = env
+    N = 1 << log2n
+    say(f"N=2^{log2n} F={F} pairs={pairs}")
+    d = synth.make_precision(n_frames=F, fft_len=N) if pairs == 2 else synth.make_correlated_noise(8, 0.3, N, F, seed_extra=5)
+    inst = pk.Instance.from_synth(d, precision="fp32", accum="fp64")
+    acc = oracle.run_instance(d)[0]
+    packed = torch.from_numpy(d["packed"]).to(dev)
+    per = N * d["n_streams"] * d["bits"] // 8
+    cut = (F // 3) * per
+    side = torch.cuda.Stream(dev)
+    with torch.cuda.stream(side):
+        counted = pk.Plan([inst], device=dev, stream=side)
+        counted.set_histograms(True)
+
+        def whole():
+            counted.reset()
+            counted.accumulate(packed)
+
+        whole()
+        got = counted.spectra()[0]
+        assert np.max(np.abs(got.cpu().numpy() - acc)) < 1e-5 * acc[:, :2].mean()
+        counted.reset()
+        counted.accumulate(packed[:cut])
+        state, n = counted.state_export()
+        counted.accumulate(packed[cut:])
+        assert torch.equal(counted.spectra()[0], got)
+        plain = pk.Plan([inst], device=dev, stream=side)
+        plain.state_import(state, n)
+        counted.reset()
+        counted.accumulate(packed[:cut])
+        a, b = plain.spectra()[0], counted.spectra()[0]
+        assert float((a - b).abs().max() / b[:, :2].mean()) < 1e-12
+        plain.accumulate(packed[cut:])
+        assert float((plain.spectra()[0] - got).abs().max() / got[:, :2].mean()) < 1e-5
+        counted.graph_capture(whole)
+        for k in range(3):
+            counted.reset()
+            counted.set_histograms(False)
+            counted.accumulate(packed[:cut * (k % 2 + 1)])
+            counted.stokes()
+            counted.reset()
+            counted.set_histograms(True)
+            counted.graph_replay()
+            assert torch.equal(counted.spectra()[0], got), k
+    torch.cuda.synchronize(dev)

@@ -99,7 +99,7 @@ struct LevelHist {
 };
 
 // one tile of the column pass: column block, pair and frame group numbered by blk
-template <int L, int COLS, int V, int BITS, int FAST, bool HIST = false>
+template <int L, int COLS, int V, int BITS, int FAST, bool HIST = false, bool GROUPED = false>
 __device__ __forceinline__ void colpass_tile(const ColArgs& a, const int blk) {
   constexpr int CPR = COLS / V;  // column groups per row
   using SC = Sched<L>;
@@ -146,26 +146,35 @@ __device__ __forceinline__ void colpass_tile(const ColArgs& a, const int blk) {
   }
   // The window of this thread's samples, the same for every frame, stays in registers (16 more of the 256 that two
   // waves per SIMD leave).  Read from L2 in every frame, half as many bytes as the intermediate, it made half-
-  // overlapped frames of 2^18 points with a Hamming window 136 us per second against 128.
+  // overlapped frames of 2^18 points with a Hamming window 136 us per second against 128.  Not so 512-point columns of two
+  // streams of 2-bit codes, which wait for their byte loads whatever the window costs, and less so with the window's loads
+  // between those of two frames: 2^18 points 43.1 us per launch against 44.4, half-overlapped 80.3 against 86.1 (the
+  // grouped launches, with other frames per tile, gain from registers there too: 191 -> 186 us for four sets).
+  constexpr bool WREG = GROUPED || !(L == 512 && BITS == 2 && FAST == 1);
   float win[V][8];
-  if (a.win) {
+  auto window = [&](auto&& put) {
 #pragma unroll
     for (int i = 0; i < 8 / R0; ++i)
 #pragma unroll
       for (int r = 0; r < R0; ++r)
 #pragma unroll
-        for (int c = 0; c < V; ++c) win[c][i * R0 + r] = a.win[(int64_t)pin<L, R0>(ts, i, r) * a.N2 + n2b + c];
-  }
+        for (int c = 0; c < V; ++c) put(c, i * R0 + r, a.win[(int64_t)pin<L, R0>(ts, i, r) * a.N2 + n2b + c]);
+  };
+  if (WREG && a.win) window([&](int c, int e, float w) { win[c][e] = w; });
   // input words are fetched one frame ahead of their use
   auto frame = [&](ColLoader<BITS, FAST, V>& ld, const int f) {
     float2 v[V][8];
     ld.template convert<L, R0>(v, a, ts, n2b, sx, sy);
     if constexpr (H) hist.count(hs, v, hrows);
     if (a.win) {
+      if constexpr (WREG) {
 #pragma unroll
-      for (int c = 0; c < V; ++c)
+        for (int c = 0; c < V; ++c)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[c][e] = make_float2(v[c][e].x * win[c][e], v[c][e].y * win[c][e]);
+          for (int e = 0; e < 8; ++e) v[c][e] = make_float2(v[c][e].x * win[c][e], v[c][e].y * win[c][e]);
+      } else {
+        window([&](int c, int e, float w) { v[c][e] = make_float2(v[c][e].x * w, v[c][e].y * w); });
+      }
     }
     // The next frame's loads and this frame's stores are issued at raised wave priority, so that they reach
     // the memory system before the other waves' arithmetic (column pass 41.3 -> 40.4 us, two integrations
@@ -238,7 +247,7 @@ __global__ void __launch_bounds__(L * COLS / (8 * V))
   const int tile = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int t = batch_task(tile_end, n_tasks, tile);
   const ColArgs a = load_const(tasks + t);
-  colpass_tile<L, COLS, V, BITS, FAST>(a, tile - (t ? tile_end[t - 1] : 0));
+  colpass_tile<L, COLS, V, BITS, FAST, false, true>(a, tile - (t ? tile_end[t - 1] : 0));
 }
 
 // Calibrated Stokes of channel k of pair p from its accumulated products (the sums of XX*, YY*, XY*):

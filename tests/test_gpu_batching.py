@@ -311,3 +311,24 @@ def test_long_instance_leaves_the_others_grouped(env, frames):
         one.reset()
         want = one.accumulate_stokes([p])[0]
         assert torch.equal(plan.spectra(i)[0], one.spectra()[0]) and torch.equal(st[i], want), i
+
+
+@pytest.mark.parametrize("log2n,hop", [(17, 1), (18, 1), (18, 2), (20, 1)])
+def test_windowed_two_bit_codes(env, log2n, hop):
+    """512-point columns of 2-bit codes read the window in every frame when launched singly and keep it in registers in
+    the grouped launches: the same spectra bitwise, and the FP64 oracle's within 1e-5 of the mean power."""
+    torch, pk, dev = env
+    N = 1 << log2n
+    d = synth.make_correlated_noise(2, 0.3, N, 4, seed_extra=log2n + hop, window="hann")
+    if hop > 1:
+        d = dict(d, hop=N // hop)
+    say(f"windowed 2-bit N=2^{log2n} hop N/{hop}")
+    packed = torch.from_numpy(d["packed"]).to(dev)
+    inst = pk.Instance.from_synth(d)
+    one, two = pk.Plan([inst], device=dev), pk.Plan([inst, inst], device=dev)
+    one.accumulate(packed)
+    two.accumulate([packed, packed])
+    got = one.spectra()[0]
+    assert torch.equal(two.spectra(0)[0], got) and torch.equal(two.spectra(1)[0], got)
+    acc = oracle.run_instance(d)[0]
+    assert np.max(np.abs(got.cpu().numpy() - acc)) < 1e-5 * acc[:, :2].mean()

@@ -155,11 +155,11 @@ ps_status ps_plan(const ps_instance* inst, int32_t n_inst, ps_plan_t* out, size_
  *   col_wg_per_cu   column-pass workgroups per CU that the frame grouping aims at (1 .. 8; default 4 for
  *                   2^13, 2 for 2^14 .. 2^16 points with FP32 passes, else 1);
  *   rowpass_slots   accumulator slots G (a power of two, 1 .. 64; 1 .. 8192 in a single pass): frame a of
- *                   the integration goes to slot a mod G, so G frame groups run in parallel; readers sum the
+ *                   the integration goes to slot a mod G (with 16-bit passes a / 16 mod G), so G frame groups run in parallel; readers sum the
  *                   slots in a fixed order.  Default: enough for about 256 row-pass workgroups (512 up to 2^18
  *                   points and for 16-bit
  *                   passes, which take no other; 2^21 / (N n_pairs) rounded down to a power of two, at most 8192, in a
- *                   single pass).
+ *                   single pass, of which an integration with level histograms uses 2^18 / (N n_pairs)).
  *   single_pass     0: the default (a single pass for FP32 transforms of 2^8 .. 2^12 points, else the
  *                   four-step passes); 1: a single pass (each workgroup transforms whole frames in LDS
  *                   and accumulates their products; 2^8 .. 2^12 points, FP32; only log2_n1 and

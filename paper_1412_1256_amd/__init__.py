@@ -233,7 +233,7 @@ class Plan:
                 raise ValueError("one schedule per instance")
             sarr = (_Schedule * len(self.instances))(*[(x or Schedule()).to_c() for x in schedules])
             _check(lib().ps_plan_scheduled(arr, sarr, len(self.instances), C.byref(h), C.byref(nbytes)))
-        self.schedules = schedules
+        self.schedules, self._tuned = schedules, tune
         self._h = h
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         # the library needs 256-byte alignment; over-allocate and offset
@@ -447,6 +447,7 @@ class Plan:
         return n.value, list(layout)
 
     def state_bytes(self, inst: int = 0) -> int:
+        """Bytes of a state of state_export()."""
         return self._state_parts(inst)[0] + 64
 
     def state_export(self, inst: int = 0):
@@ -481,6 +482,9 @@ class Plan:
         _, _, _, _, n2, slots, block, waiting = layout
         sched = (self.schedules[inst] if self.schedules else None) or Schedule()
         I, torch = self.instances[inst], self.torch
+        if self._tuned:
+            raise ValueError(f"instance {inst}: a state without its layout may be of another tuned schedule; give the plan "
+                             "the schedule that the state was saved with")
         slot = (size - waiting) // slots
         if block > 1:
             # 16-bit passes: one slot, or as many as now in blocks of four frames; all slots' sums go into the first

@@ -45,6 +45,7 @@ def cpu_plan(*instances):
     p = pk.Plan.__new__(pk.Plan)
     p.torch, p.instances, p.device = torch, list(instances), torch.device("cpu")
     p.workspace = torch.empty(256, dtype=torch.uint8)
+    p._tuned = False
     p._h = None
     return p
 
@@ -236,3 +237,16 @@ def test_tuned_schedules_belong_to_a_build(monkeypatch, tmp_path):
     a, b = tmp_path / "a.so", tmp_path / "b.so"
     a.write_bytes(b"one"), b.write_bytes(b"two")
     assert autotune.build_id(str(a)) != autotune.build_id(str(b)) and len(autotune.build_id()) == 16
+
+
+def test_untagged_state_of_a_tuned_plan(state_plan):
+    """A tuner may pick another schedule than it did for the plan that saved the state: refused, unless the schedule is
+    the caller's own; states with their layout are compared with it."""
+    make, taken = state_plan
+    sched = S(5, rowpass_slots=8, single_pass=2)
+    for tuned in (False, True):
+        plan = make(sched, fft_len=1 << 10)
+        plan._tuned = tuned
+        assert (taken(plan, state_of(plan, tagged=False)) is None) == tuned
+        assert taken(plan, state_of(plan)) is not None
+        assert taken(plan, state_of(make(S(4, rowpass_slots=8, single_pass=2), fft_len=1 << 10))) is None
